@@ -110,6 +110,45 @@ def test_advect_full_2048_sampled():
 # ---------------------------------------------------------------------------
 # ftle_advect_rk4_grid: a velocity field sampled on a regular grid
 # ---------------------------------------------------------------------------
+@pytest.mark.parametrize("flow,shift", [("double_gyre", 0.0), ("double_gyre", 2.0 ** 29), ("double_gyre", 2.0 ** 31),
+                                        ("abc", 0.0), ("abc", 2.0 ** 29), ("abc", 2.0 ** 31)])
+def test_advect_reach(flow, shift):
+    """Both step forms, either side of the reach (2^30) that picks between them:
+    particles shifted along y (double gyre) or every axis (ABC), mixed with
+    unshifted ones and with non-finite ones in the same waves.
+
+    Tolerance: each of the 5 steps rounds the position by at most half its
+    spacing u, and the oracle's argument pi y carries at most another u of
+    phase; the flow stretches these by less than exp(10 * 0.1) < 3 on the way:
+    (5 / 2 + 1) * 3 u < 16 u.  Unshifted particles: 1e-9, as above."""
+    x = meshes.jittered_tri_grid(16, 12, seed=9)[0] if flow == "double_gyre" else meshes.kuhn_tet_grid(6)[0]
+    n, t0, T, dt = x.shape[0], 0.3, 0.1, 0.02
+    far = np.arange(n) % 3 == 0
+    x = x.copy()
+    if flow == "double_gyre":
+        x[far, 1] += shift
+    else:
+        x[far] += shift
+    ref = oracle.advect_rk4(flow, x, t0, T, dt)
+    bad = np.arange(n) % 17 == 1
+    xb = x.copy()
+    xb[bad, 0] = np.where(np.arange(bad.sum()) % 2, np.nan, np.inf)
+    got = F.advect_rk4(flow, torch.as_tensor(xb, device=DEV), t0, T, dt).cpu().numpy()
+    assert np.isnan(got[bad, 0]).all()
+    tol = np.where(far, 16 * np.spacing(max(shift, 1.0)), 1e-9) if shift else np.full(n, 1e-9)
+    assert np.all(np.abs(got - ref)[~bad] <= tol[~bad, None])
+
+
+def test_advect_walls_are_kept():
+    """A double-gyre particle on a wall (y an integer, x = 0) stays on it exactly."""
+    r = np.random.default_rng(3)
+    x = np.stack([r.random(200) * 2, r.integers(-1, 3, 200)], 1).astype(np.float64)
+    x[150:, 0], x[150:, 1] = 0.0, r.random(50)
+    got = F.advect_rk4("double_gyre", torch.as_tensor(x, device=DEV), 0.2, 15.0, 0.01).cpu().numpy()
+    assert np.array_equal(got[:150, 1], x[:150, 1])
+    assert np.array_equal(got[150:, 0], x[150:, 0])
+
+
 def _gyre_grid(nx, ny, times):
     """The double gyre at the nodes of an nx x ny grid over [0, 2] x [0, 1]."""
     return flows.sampled_field(flows.double_gyre_velocity, [0.0, 0.0], [2.0 / (nx - 1), 1.0 / (ny - 1)], (nx, ny),
