@@ -283,6 +283,52 @@ def test_advect_grid_full_2048_sampled():
     assert np.all(err <= 1e-9)
 
 
+@pytest.mark.parametrize("dim,slices,n", [(2, 5, 4096 * 64), (2, 1, 8192 * 64), (3, 3, 2048 * 64), (3, 1, 4096 * 64)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_advect_grid_launch_forms(dim, slices, n, dtype):
+    """A particle's path does not depend on the launch: one more than n particles
+    take single-wave workgroups, the rest of the calls four-wave ones, with the
+    window as numbers or per particle; all bit for bit the same, some particles
+    outside the box or not finite."""
+    g = torch.Generator(device=DEV).manual_seed(dim * 10 + slices)
+    shape = (slices,) + (9, 11, 13)[:dim] + (dim,)
+    vel = (torch.rand(shape, generator=g, device=DEV) - 0.5).to(dtype)
+    x = torch.rand(n + 1, dim, generator=g, device=DEV, dtype=torch.float64) * 1.4 - 0.2
+    x[::1001, 0] = float("nan")
+    x[5::1001, 1] = float("inf")
+    spacing = [0.125, 0.1, 0.1][:dim]
+    args = (vel, [0.0] * dim, spacing, 0.0, 0.3)
+    many = F.advect_rk4_grid(*args, x, 0.1, 0.7, 0.09)
+    few = x[-1000:].contiguous()
+    one = F.advect_rk4_grid(*args, few, 0.1, 0.7, 0.09)
+    same = lambda a, b: torch.equal(a.view(torch.int64), b.view(torch.int64))   # noqa: E731 - NaN included
+    assert same(many[-1000:].contiguous(), one)
+    per = lambda v: torch.full((1000,), v, dtype=torch.float64, device=DEV)   # noqa: E731
+    assert same(F.advect_rk4_grid(*args, few, per(0.1), per(0.7), 0.09), one)
+    ref = oracle.advect_rk4_grid(vel.double().cpu().numpy(), [0.0] * dim, spacing, 0.0, 0.3, few.cpu().numpy(), 0.1,
+                                 0.7, 0.09)
+    fin = torch.isfinite(few).all(1).cpu().numpy()
+    assert np.abs(one.cpu().numpy()[fin] - ref[fin]).max() < 1e-9
+
+
+def test_advect_grid_wide_field():
+    """A field of 4 GiB and more (64-bit offsets) against a coarse one of the same
+    linear velocity (its node values are exact in float32 on both grids): equal
+    up to the arithmetic's roundings, 12 steps of at most a few units in the
+    last place of positions below 2."""
+    m = 16384 + 1
+    ax = torch.arange(m, device=DEV, dtype=torch.float32) * 2.0 ** -13
+    vel = torch.empty(2, m, m, 2, device=DEV)
+    vel[0, :, :, 0], vel[0, :, :, 1] = (ax * 0.25)[:, None], (ax * -0.25)[None, :]
+    vel[1] = vel[0] * 2.0
+    coarse = vel[:, ::4096, ::4096].contiguous()
+    assert vel.numel() * 4 >= 2 ** 32
+    x = torch.rand(500, 2, generator=torch.Generator(device=DEV).manual_seed(1), device=DEV, dtype=torch.float64) + 0.5
+    fine = F.advect_rk4_grid(vel, [0.0, 0.0], [2.0 ** -13] * 2, 0.0, 2.0, x, 0.0, 1.2, 0.1)
+    ref = F.advect_rk4_grid(coarse, [0.0, 0.0], [0.5] * 2, 0.0, 2.0, x, 0.0, 1.2, 0.1)
+    assert (fine - ref).abs().max().item() <= 12 * 8 * 2.0 ** -52
+
+
 def test_wrappers_reject_bad_outputs():
     """The Python wrappers check the output tensor (shape, dtype, device, not
     the input) and the grid's origin and spacing lengths before any launch."""
