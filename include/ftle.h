@@ -132,8 +132,8 @@ ftle_status ftle_create_mesh_from_csr(int dim, int64_t n_points, const void* coo
  * inverse normal matrices; with FTLE_STENCIL_AXIS also the axis stencil and
  * its transpose (the adjoint's tiles).  The mesh is the one ftle_create_mesh
  * builds from the same arguments: the same permutation, stencil, tiles and
- * record bytes, hence bit-identical results from every call on it.  The host steers the steps from small downloads (bounds,
- * a 2^16-pair sample of the caller's order, tile sizes); the stencil and the
+ * record bytes, hence bit-identical results from every call on it.  The host
+ * steers the steps from small downloads (bounds, tile sizes); the stencil and the
  * records stay on the device, and ftle_mesh_get_csr / ftle_mesh_get_tiles
  * copy them out when asked.
  *   coords   device pointer (current device), n_points x dim, float or

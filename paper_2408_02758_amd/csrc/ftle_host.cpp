@@ -986,8 +986,8 @@ std::vector<double> checked_coords(int dim, int64_t n_points, const void* coords
 // the same result as build_mesh with the one-ring stencil, with every pass
 // over points, cells or stencil entries in the kernels of ftle_meshbuild.hip
 // and ftle_neighbours.hip.  The host keeps the control: the bounding box
-// reduction over workgroups, the caller-order test on a 2^16-pair sample, the
-// tile-size halving and the record offsets, each from a small download.
+// reduction over workgroups, the tile-size halving and the record offsets,
+// each from a small download.
 // ---------------------------------------------------------------------------
 
 // A device allocation freed on scope exit unless released.
@@ -1273,7 +1273,7 @@ ftle_mesh_t build_device(int dim, int64_t n, const void* coords, ftle_dtype dtyp
     const int nb = (int)std::min<int64_t>(1024, (n + 255) / 256);
     int64_t ms = 0, stride = 0;
     order_sample(n, &ms, &stride);
-    const size_t phase_sort = Arena::round((size_t)nb * 2 * dim * 8 + 8) + Arena::round((size_t)ms * 2 * dim * 8) +
+    const size_t phase_sort = Arena::round((size_t)nb * 2 * dim * 8 + 8) + Arena::round(36) +
                               Arena::round((size_t)n * 8) + Arena::round(mb_sort_scratch_bytes(n));
     ScratchLease arena_buf(std::max(phase_sort, stencil_bytes), s);
     Arena arena;
@@ -1305,18 +1305,19 @@ ftle_mesh_t build_device(int dim, int64_t n, const void* coords, ftle_dtype dtyp
             }
         double unit[3] = {1, 1, 1}, range = 1.0;
         morton_units(dim, n, lo, hi, unit, &range);
-        std::vector<double> pairs((size_t)ms * 2 * dim);
-        if (ms) {
-            double* d_pairs = arena.take<double>(pairs.size() * 8);
-            check_hip(mb_gather_pairs(dim, f64, m->d_x, ms, stride, d_pairs, s), "sample kernel");
-            to_host(pairs.data(), d_pairs, pairs.size() * 8, s);
-        }
-        const MortonParams mp = morton_params(dim, lo, unit, range, order_axis_from_pairs(dim, ms, pairs.data(), unit));
+        // the codes' parameters without and with a caller-order axis (which one
+        // it is does not change them); the Morton kernel picks by the sample's
+        // counts, and the sort takes the bits of either
+        const MortonParams plain = morton_params(dim, lo, unit, range, -1), axis = morton_params(dim, lo, unit, range, 0);
+        uint32_t* counts = arena.take<uint32_t>(36);
+        check_hip(hipMemsetAsync(counts, 0, 36, s), "hipMemsetAsync");
+        check_hip(mb_order_counts(dim, f64, m->d_x, ms, stride, plain, counts, s), "sample kernel");
         uint64_t* key = arena.take<uint64_t>((size_t)n * 8);
         void* scratch = arena.take<void>(mb_sort_scratch_bytes(n));
-        check_hip(mb_morton(dim, f64, m->d_x, n, mp, key, perm, s), "Morton kernel");
+        check_hip(mb_morton(dim, f64, m->d_x, n, plain, axis, counts, ms, key, perm, s), "Morton kernel");
         uint32_t* sorted = nullptr;
-        check_hip(mb_sort(key, perm, n, morton_key_bits(dim, mp, range), scratch, &sorted, s), "radix sort");
+        const int bits = std::max(morton_key_bits(dim, plain, range), morton_key_bits(dim, axis, range));
+        check_hip(mb_sort(key, perm, n, bits, scratch, &sorted, s), "radix sort");
         if (sorted != perm)
             check_hip(hipMemcpyAsync(perm, sorted, (size_t)n * 4, hipMemcpyDeviceToDevice, s), "hipMemcpyAsync");
     } else {

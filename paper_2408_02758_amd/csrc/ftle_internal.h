@@ -232,8 +232,10 @@ struct MortonParams {
 //   mb_bbox: per-workgroup minima and maxima (part[b * 2 dim + d], then the
 //     maxima at + dim) over nblocks workgroups; *first_bad (set to ~0 before)
 //     gets the lowest point with a coordinate that is not finite
-//   mb_gather_pairs: sample k = points k stride and k stride + 1, as float64
-//   mb_morton: codes key[i] and values val[i] = i
+//   mb_order_counts: counts (3 dim values, zeroed before) of a sample of m
+//     steps between consecutive caller points, for the caller-order axis test
+//   mb_morton: codes key[i] and values val[i] = i, by `axis` (its fast axis
+//     found from the counts) where the caller's order has one, else by `plain`
 //   mb_sort: stable sort of (key, val) by the low key_bits bits of key;
 //     *sorted_val is val or a buffer inside scratch (mb_sort_scratch_bytes)
 //   mb_invert: inv[perm[r]] = r
@@ -247,9 +249,10 @@ struct MortonParams {
 //   mb_normal_inverse: the 3D inverse normal matrices (caller order)
 hipError_t mb_bbox(int dim, bool f64, const void* x, int64_t n, double* part, int nblocks,
                    unsigned long long* first_bad, hipStream_t s);
-hipError_t mb_gather_pairs(int dim, bool f64, const void* x, int64_t m, int64_t stride, double* out, hipStream_t s);
-hipError_t mb_morton(int dim, bool f64, const void* x, int64_t n, const MortonParams& mp, uint64_t* key,
-                     uint32_t* val, hipStream_t s);
+hipError_t mb_order_counts(int dim, bool f64, const void* x, int64_t m, int64_t stride, const MortonParams& mp,
+                           uint32_t* counts, hipStream_t s);
+hipError_t mb_morton(int dim, bool f64, const void* x, int64_t n, const MortonParams& plain, const MortonParams& axis,
+                     const uint32_t* counts, int64_t m, uint64_t* key, uint32_t* val, hipStream_t s);
 size_t mb_sort_scratch_bytes(int64_t n);
 hipError_t mb_sort(uint64_t* key, uint32_t* val, int64_t n, int key_bits, void* scratch, uint32_t** sorted_val,
                    hipStream_t s);

@@ -141,6 +141,27 @@ def test_tile_sizes(tile_log2):
     assert_same_mesh(x, cells, "f32", tile_log2=tile_log2)
 
 
+@pytest.mark.parametrize("dim,order", [(2, "y"), (2, "skip"), (2, "half"), (2, "few"), (2, "64"), (3, "y"), (3, "z")])
+def test_caller_order_axis(dim, order):
+    """Every answer of the caller-order axis test: along y or z; two spacings a
+    step or half of them zero (no axis); below and at the sample's 64 points."""
+    if dim == 2:
+        nx, ny = {"few": (9, 7), "64": (8, 8)}.get(order, (40, 30))
+        x, cells = meshes.jittered_tri_grid(nx, ny, seed=8, jitter=0.1)
+        i, j = np.meshgrid(np.arange(nx), np.arange(ny), indexing="xy")
+        i, j = i.ravel(), j.ravel()
+        key = {"y": i * ny + j, "skip": j * nx + (i % 2) * nx * ny + i, "half": (j // 2) * 2 * nx + 2 * i + j % 2}.get(
+            order, j * nx + i)
+    else:
+        x, cells = meshes.kuhn_tet_grid(11)
+        k, j, i = (a.ravel() for a in np.meshgrid(*[np.arange(11)] * 3, indexing="ij"))
+        key = (i * 11 + k) * 11 + j if order == "y" else (j * 11 + i) * 11 + k
+    rank = np.argsort(np.argsort(key, kind="stable"), kind="stable")
+    y = np.empty_like(x)
+    y[rank] = x
+    assert_same_mesh(y, rank[cells].astype(np.int32))
+
+
 def test_no_reorder():
     x, cells = meshes.jittered_tri_grid(60, 45, seed=6)
     assert_same_mesh(x, cells, "f32", reorder=False)
