@@ -1168,23 +1168,28 @@ std::vector<Extent> device_extents(int dim, bool f64, int64_t n, int tile_points
     return out;
 }
 
-// The records of the tiles `ext` (two passes: sizes and rows, then the
-// records at their offsets), into ts (meta on host and device, records on
-// the device).
+// The records of the tiles `ext` (written to a stage that has room for each
+// tile's largest record, sized, then moved to their offsets), into ts (meta on
+// host and device, records on the device).
 void device_tiles(const std::vector<Extent>& ext, const int64_t* row_ptr, const int32_t* col, const int32_t* perm,
                   TileSet& ts, Arena& arena, hipStream_t s)
 {
     const size_t T = ext.size();
-    std::vector<int64_t> ranges(2 * T), row_base(T);
-    int64_t entries = 0;
+    std::vector<int64_t> ranges(2 * T);
+    std::vector<uint32_t> stage_off(T);
+    uint64_t stage_units = 0;   // of 16 bytes
+    uint32_t max_words = 0;
     for (size_t t = 0; t < T; ++t) {
         ranges[2 * t] = ext[t].b;
         ranges[2 * t + 1] = ext[t].e;
-        row_base[t] = entries;
-        entries += 3 * (int64_t)ext[t].nw;
+        if (stage_units > UINT32_MAX) fail(FTLE_ERR_UNSUPPORTED, "tile records exceed 64 GiB");
+        stage_off[t] = (uint32_t)stage_units;
+        const uint32_t P = (uint32_t)(ext[t].e - ext[t].b), H = ext[t].H;
+        stage_units += rec_layout(P, H, ext[t].nw, P + H, P).bytes / 16;
+        max_words = std::max(max_words, ext[t].nw);
     }
-    // the row buffer from the arena when it fits there, else its own allocation
-    const size_t need = Arena::round(T * 16) * 2 + Arena::round(T * 8) + Arena::round((size_t)entries * 2);
+    // the stage from the arena when it fits there, else its own allocation
+    const size_t need = Arena::round(T * 16) * 2 + Arena::round(T * 4) + Arena::round((size_t)stage_units * 16);
     DevBuf own;
     Arena local;
     if (arena.at + need > arena.size) {
@@ -1194,15 +1199,14 @@ void device_tiles(const std::vector<Extent>& ext, const int64_t* row_ptr, const 
     }
     Arena& a = own.p ? local : arena;
     int64_t* d_ranges = a.take<int64_t>(T * 16);
-    int64_t* d_base = a.take<int64_t>(T * 8);
+    uint32_t* d_off = a.take<uint32_t>(T * 4);
     uint32_t* d_counts = a.take<uint32_t>(T * 16);
-    uint16_t* d_rows = a.take<uint16_t>((size_t)entries * 2);
+    unsigned char* d_stage = a.take<unsigned char>((size_t)stage_units * 16);
     to_device(d_ranges, ranges.data(), T * 16, s);
-    to_device(d_base, row_base.data(), T * 8, s);
+    to_device(d_off, stage_off.data(), T * 4, s);
     const uint32_t* uperm = reinterpret_cast<const uint32_t*>(perm);
-    check_hip(mb_tile_record(false, row_ptr, col, uperm, d_ranges, (int64_t)T, d_base, d_rows, d_counts, nullptr,
-                             nullptr, s),
-              "tile record kernel (sizes)");
+    check_hip(mb_tile_record(row_ptr, col, uperm, d_ranges, (int64_t)T, max_words, d_off, d_counts, d_stage, s),
+              "tile record kernel");
     std::vector<uint32_t> counts(4 * T);
     to_host(counts.data(), d_counts, T * 16, s);
     ts.meta.resize(T);
@@ -1230,10 +1234,9 @@ void device_tiles(const std::vector<Extent>& ext, const int64_t* row_ptr, const 
     ts.rec_bytes = (int64_t)off * 16;
     ts.d_meta = dev_upload(ts.meta.data(), T * sizeof(TileMeta));
     ts.d_rec = dev_upload(nullptr, (size_t)ts.rec_bytes);
-    check_hip(hipMemsetAsync(ts.d_rec, 0, (size_t)ts.rec_bytes, s), "hipMemsetAsync");
-    check_hip(mb_tile_record(true, row_ptr, col, uperm, d_ranges, (int64_t)T, d_base, d_rows, nullptr,
-                             static_cast<const TileMeta*>(ts.d_meta), static_cast<unsigned char*>(ts.d_rec), s),
-              "tile record kernel (records)");
+    check_hip(mb_compact_records(d_off, static_cast<const TileMeta*>(ts.d_meta), (int64_t)T, d_stage,
+                                 static_cast<unsigned char*>(ts.d_rec), s),
+              "tile record kernel (compaction)");
     check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
 }
 

@@ -243,9 +243,10 @@ struct MortonParams {
 //     outside [0, n) or a repeated point sets *flag and lowers *first
 //   mb_tile_extent: for ranges [b, e) (int64 pairs) of the Morton order, the
 //     halo size (kMaxStaged + 1 when larger) and the padded stencil words
-//   mb_tile_record: write = false sizes each tile's record (counts[4 t] =
-//     explicit words, runs, explicit rows, all words) and fills the row
-//     buffer; write = true writes the records at 16 meta[t].rec_off bytes
+//   mb_tile_record: each tile's record at stage + 16 stage_off[t] (room for
+//     rec_layout(P, H, nwf, P + H, P)) and counts[4 t] = explicit words, runs,
+//     explicit rows, all words; max_words: the largest tile's words
+//   mb_compact_records: record t from there to rec + 16 meta[t].rec_off
 //   mb_normal_inverse: the 3D inverse normal matrices (caller order)
 hipError_t mb_bbox(int dim, bool f64, const void* x, int64_t n, double* part, int nblocks,
                    unsigned long long* first_bad, hipStream_t s);
@@ -262,9 +263,11 @@ hipError_t mb_relabel(int dim, const int32_t* cells, int64_t n_cells, int64_t n,
                       int* flag, unsigned long long* first, hipStream_t s);
 hipError_t mb_tile_extent(const int64_t* row_ptr, const int32_t* col, const int64_t* ranges, int64_t n_ranges,
                           uint32_t* halo_words, hipStream_t s);
-hipError_t mb_tile_record(bool write, const int64_t* row_ptr, const int32_t* col, const uint32_t* perm,
-                          const int64_t* ranges, int64_t n_tiles, const int64_t* row_base, uint16_t* rowbuf,
-                          uint32_t* counts, const TileMeta* meta, unsigned char* rec, hipStream_t s);
+hipError_t mb_tile_record(const int64_t* row_ptr, const int32_t* col, const uint32_t* perm, const int64_t* ranges,
+                          int64_t n_tiles, uint32_t max_words, const uint32_t* stage_off, uint32_t* counts,
+                          unsigned char* stage, hipStream_t s);
+hipError_t mb_compact_records(const uint32_t* stage_off, const TileMeta* meta, int64_t n_tiles,
+                              const unsigned char* stage, unsigned char* rec, hipStream_t s);
 hipError_t mb_normal_inverse(bool f64, const int64_t* row_ptr, const int32_t* col, const uint32_t* perm,
                              const void* x, int64_t n, void* out, hipStream_t s);
 //   mb_axis_stencil: the axis stencil's slots (n x 2 dim, -1 absent) and

@@ -27,8 +27,8 @@
 //   tile_extent     for candidate Morton ranges: halo points and stencil words
 //   tile_record     the record of each tile (the layout in ftle_internal.h):
 //                   own points and halo in caller order, index runs, rows as
-//                   sorted local slots, shift rows; a first pass sizes the
-//                   records, a second writes them
+//                   sorted local slots, shift rows; compact_records then moves
+//                   the records together
 //   normal_inverse  the 3D normal matrix inverse per point (float64)
 //   axis_slots / axis_fill
 //                   the axis stencil from the one-ring rows, then its CSR
@@ -308,25 +308,27 @@ __global__ void __launch_bounds__(256) check_relabel(const int32_t* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// tiles.  Shared by both kernels: the halo of Morton range [b, e) (the
+// tiles.  Shared by the extents and the records: the halo of Morton range [b, e) (the
 // stencil's neighbours outside it), gathered in an LDS hash set of Morton
 // positions (open addressing).
 // ---------------------------------------------------------------------------
-constexpr int kTileThreads = 256;
+constexpr int kTileThreads = 512, kExtentThreads = 256;
+constexpr int kTileWaves = kTileThreads / 64;
 constexpr int kHashSlots = 2 * kMaxStaged;   // at most kMaxStaged keys are ever kept
-constexpr int kChunk = 4;                    // stencil entries a lane loads at once
-constexpr int kRowScratch = 32;              // row entries a lane sorts in LDS (longer rows: in global memory)
+constexpr int kChunk = 8;                    // stencil entries a lane loads at once
+constexpr int kRowRegs = 32;                 // row entries a lane sorts in registers (longer rows: the workgroup)
 
 __device__ inline uint32_t tile_hash(int32_t v) { return ((uint32_t)v * 2654435761u) >> 21; }   // 11 bits
 
 // Insert every outside neighbour of rows [b, e); keys[] = -1 before.  Returns
 // (to every lane) the number of distinct keys, or kMaxStaged + 1 when more
 // would be needed.  hlist gets the keys in insertion order.
+template <int THREADS>
 __device__ inline int gather_halo(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int64_t b,
                                   int64_t e, int32_t* keys, int32_t* hlist, int* count, int t)
 {
     static_assert(kHashSlots == 1 << 11, "tile_hash gives 11 bits");
-    for (int64_t r = b + t; r < e; r += kTileThreads) {
+    for (int64_t r = b + t; r < e; r += THREADS) {
         if (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > kMaxStaged) break;
         const int64_t p0 = row_ptr[r], p1 = row_ptr[r + 1];
         // kChunk entries loaded together, then inserted (a load past the row
@@ -357,16 +359,9 @@ __device__ inline int gather_halo(const int64_t* __restrict__ row_ptr, const int
     return cnt > kMaxStaged ? kMaxStaged + 1 : cnt;
 }
 
-__device__ inline int lookup_halo(const int32_t* keys, const uint16_t* slot, int32_t c)
-{
-    uint32_t h = tile_hash(c);
-    while (keys[h] != c) h = (h + 1) & (kHashSlots - 1);
-    return slot[h];
-}
-
 // For each candidate range: its halo size (kMaxStaged + 1 when over) and its
 // stencil words (rows padded to multiples of 3).
-__global__ void __launch_bounds__(kTileThreads) tile_extent(const int64_t* __restrict__ row_ptr,
+__global__ void __launch_bounds__(kExtentThreads) tile_extent(const int64_t* __restrict__ row_ptr,
                                                             const int32_t* __restrict__ col,
                                                             const int64_t* __restrict__ ranges,
                                                             uint32_t* __restrict__ halo_words)
@@ -378,17 +373,17 @@ __global__ void __launch_bounds__(kTileThreads) tile_extent(const int64_t* __res
     const int t = (int)threadIdx.x;
     const int tb = xcd_tile((int)blockIdx.x, (int)gridDim.x);   // XCD-contiguous ranges
     const int64_t b = ranges[2 * tb], e = ranges[2 * tb + 1];
-    for (int i = t; i < kHashSlots; i += kTileThreads) keys[i] = -1;
+    for (int i = t; i < kHashSlots; i += kExtentThreads) keys[i] = -1;
     if (t == 0) {
         count = 0;
         words = 0;
     }
     __syncthreads();
     unsigned long long w = 0;
-    for (int64_t r = b + t; r < e; r += kTileThreads) w += (uint64_t)((row_ptr[r + 1] - row_ptr[r] + 2) / 3);
+    for (int64_t r = b + t; r < e; r += kExtentThreads) w += (uint64_t)((row_ptr[r + 1] - row_ptr[r] + 2) / 3);
     atomicAdd(&words, w);
     int H = kMaxStaged + 1;
-    if (e - b <= kMaxStaged) H = gather_halo(row_ptr, col, b, e, keys, hlist, &count, t);
+    if (e - b <= kMaxStaged) H = gather_halo<kExtentThreads>(row_ptr, col, b, e, keys, hlist, &count, t);
     __syncthreads();
     if (t == 0) {
         halo_words[2 * tb] = (uint32_t)H;
@@ -396,272 +391,419 @@ __global__ void __launch_bounds__(kTileThreads) tile_extent(const int64_t* __res
     }
 }
 
-// In-LDS bitonic sort of m (<= 1024) 64-bit keys, padded with ~0 to a power of two.
-__device__ inline void bitonic_sort64(uint64_t* s, int m, int t)
+// Block-wide exclusive sum of per-lane values; returns the lane's prefix and
+// the total in total.  part: kTileWaves words.
+__device__ inline uint32_t block_excl(uint32_t v, uint32_t* part, uint32_t& total, int t)
+{
+    uint32_t incl = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t u = __shfl_up(incl, off);
+        if ((t & 63) >= off) incl += u;
+    }
+    __syncthreads();   // part may still be read from the last call
+    if ((t & 63) == 63) part[t >> 6] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kTileWaves; ++w) {
+        const uint32_t u = part[w];
+        if (w < (t >> 6)) before += u;
+        total += u;
+    }
+    return before + incl - v;
+}
+
+// Bitonic sort of m <= 2 kTileThreads 64-bit keys in s (ascending, in place):
+// lane t holds keys t and t + kTileThreads; partners within a wave exchange by
+// lane shuffles, without a barrier (39 of the 45 steps of 512 keys), the others
+// through s.
+__device__ inline void sort_keys(uint64_t* s, int m, int t)
 {
     int p2 = 1;
     while (p2 < m) p2 <<= 1;
-    for (int i = m + t; i < p2; i += kTileThreads) s[i] = ~0ull;
-    __syncthreads();
+    uint64_t v[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) v[e] = t + e * kTileThreads < m ? s[t + e * kTileThreads] : ~0ull;
     for (int size = 2; size <= p2; size <<= 1)
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = t; i < p2; i += kTileThreads) {
-                const int j = i ^ stride;
-                if (j > i) {
-                    const bool up = (i & size) == 0;
-                    const uint64_t a = s[i], c = s[j];
-                    if ((a > c) == up) {
-                        s[i] = c;
-                        s[j] = a;
-                    }
+            if (stride == kTileThreads) {   // p2 = 2 kTileThreads: both in this lane, ascending
+                if (v[0] > v[1]) {
+                    const uint64_t u = v[0];
+                    v[0] = v[1];
+                    v[1] = u;
                 }
+                continue;
             }
-            __syncthreads();
+            if (stride >= 64) {
+                __syncthreads();
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    if (t + e * kTileThreads < p2) s[t + e * kTileThreads] = v[e];
+                __syncthreads();
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int i = t + e * kTileThreads;
+                if (i - (t & 63) >= p2) continue;   // whole waves past the keys
+                uint64_t o;
+                if (stride >= 64) {
+                    o = i < p2 ? s[i ^ stride] : ~0ull;
+                } else {
+                    const uint32_t lo = __shfl_xor((uint32_t)v[e], stride), hi = __shfl_xor((uint32_t)(v[e] >> 32), stride);
+                    o = (uint64_t)hi << 32 | lo;
+                }
+                const bool keep_min = ((i & stride) == 0) == ((i & size) == 0);
+                v[e] = keep_min == (v[e] < o) ? v[e] : o;
+            }
         }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+        if (t + e * kTileThreads < m) s[t + e * kTileThreads] = v[e];
+    __syncthreads();
 }
 
-// Block-wide exclusive sum of per-lane values; returns the lane's prefix and
-// leaves the total in *total.
-__device__ inline uint32_t block_excl(uint32_t v, uint32_t* s, uint32_t* total, int t)
+// Batcher's odd-even merge sort of N values in registers, ascending.
+template <int LO, int N, int R, int M>
+__device__ inline void odd_even_merge(uint32_t (&v)[M])
 {
-    s[t] = v;
-    __syncthreads();
-    for (int off = 1; off < kTileThreads; off <<= 1) {
-        const uint32_t u = t >= off ? s[t - off] : 0u;
-        __syncthreads();
-        s[t] += u;
-        __syncthreads();
+    auto order = [&](int i, int j) {
+        const uint32_t a = min(v[i], v[j]), b = max(v[i], v[j]);
+        v[i] = a;
+        v[j] = b;
+    };
+    if constexpr (2 * R < N) {
+        odd_even_merge<LO, N, 2 * R>(v);
+        odd_even_merge<LO + R, N, 2 * R>(v);
+#pragma unroll
+        for (int i = LO + R; i + R < LO + N; i += 2 * R) order(i, i + R);
+    } else {
+        order(LO, LO + R);
     }
-    const uint32_t incl = s[t];
-    if (t == kTileThreads - 1) *total = incl;
-    __syncthreads();
-    return incl - v;
+}
+template <int LO, int N, int M>
+__device__ inline void odd_even_sort(uint32_t (&v)[M])
+{
+    if constexpr (N > 1) {
+        odd_even_sort<LO, N / 2>(v);
+        odd_even_sort<LO + N / 2, N / 2>(v);
+        odd_even_merge<LO, N, 1>(v);
+    }
 }
 
-// One tile per workgroup.  WRITE = false: the record's counts go to
-// counts[4 t] = {nw, nr, nx, nwf}, and each row (its neighbours' slots,
-// ascending, padded with the point's own slot) to rowbuf from row_base[t].
-// WRITE = true: the record is written at rec + 16 meta[t].rec_off, the rows
-// read back from rowbuf.
-template <bool WRITE>
-__global__ void __launch_bounds__(kTileThreads) tile_record(const int64_t* __restrict__ row_ptr,
+// LDS of tile_record besides its row words.
+struct TileScratch {
+    int32_t keys[kHashSlots];         // halo hash set (Morton positions)
+    uint16_t hslot[kHashSlots];       // their slots
+    uint64_t sort[kMaxStaged];        // sort keys; the halo in insertion order before; counters and long rows after
+    uint32_t caller[kMaxStaged];      // caller index of each staged slot
+    uint16_t own_slot[kMaxStaged];    // slot of own point b + i
+    uint16_t woff[kMaxStaged + 8];    // row l's first word
+    uint32_t part[kTileWaves];
+    uint32_t smask[kMaxStaged / 32], spre[kMaxStaged / 32];                        // per group of 32 slots
+    uint32_t mask[kMaxStaged / 32], pre[kMaxStaged / 32], last[kMaxStaged / 32];
+    int count, n_long;
+};
+
+// The slot of Morton position c in the tile of P points from b.
+__device__ inline uint32_t slot_of(const TileScratch& q, int64_t b, int P, int32_t c)
+{
+    const uint32_t o = (uint32_t)(c - (int32_t)b);
+    if (o < (uint32_t)P) return q.own_slot[o];
+    uint32_t h = tile_hash(c);
+    while (q.keys[h] != c) h = (h + 1) & (kHashSlots - 1);
+    return q.hslot[h];
+}
+
+// A row of at most N entries (stencil entries col[p0, p0 + len), len > 0) into
+// its words, ascending by slot, padded with the row's own slot l.
+template <int N>
+__device__ inline void short_row(const TileScratch& q, const int32_t* __restrict__ col, int64_t b, int P, int64_t p0,
+                                 int len, uint32_t l, uint32_t* out)
+{
+    uint32_t v[N];
+    // a batch of entries' loads together, then the first probe of each (the
+    // tables' reads then overlap), then the few that collided
+    constexpr int kBatch = N <= 16 ? 16 : 8;   // (registers)
+#pragma unroll
+    for (int k0 = 0; k0 < N; k0 += kBatch) {
+        int32_t c[kBatch];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) c[k] = col[p0 + min(k0 + k, len - 1)];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            const uint32_t o = (uint32_t)(c[k] - (int32_t)b), h = tile_hash(c[k]);
+            const bool own = o < (uint32_t)P;
+            const int32_t found = q.keys[h];
+            uint32_t s = own ? q.own_slot[o] : q.hslot[h];
+            if (!own && found != c[k]) s = slot_of(q, b, P, c[k]);
+            v[k0 + k] = k0 + k < len ? s : 0xffffu;
+        }
+    }
+    odd_even_sort<0, N>(v);
+    const int nw = (len + 2) / 3;
+#pragma unroll
+    for (int w = 0; w < (N + 2) / 3; ++w) {
+        if (w < nw) {
+            const uint32_t v1 = 3 * w + 1 < N ? v[3 * w + 1 < N ? 3 * w + 1 : 0] : 0xffffu;
+            const uint32_t v2 = 3 * w + 2 < N ? v[3 * w + 2 < N ? 3 * w + 2 : 0] : 0xffffu;
+            uint32_t word = v[3 * w] | (3 * w + 1 < len ? v1 : l) << 10 | (3 * w + 2 < len ? v2 : l) << 20;
+            if (w == nw - 1) word |= (uint32_t)(3 * nw - len) << 30;
+            out[w] = word;
+        }
+    }
+}
+
+// The record of one tile per workgroup, in one pass: written to
+// stage + 16 stage_off[t], where the largest record of a tile with these
+// points, halo and words has room; its counts go to counts[4 t] = {nw, nr, nx,
+// nwf}, and compact_records moves the records to their final places.  The
+// rows are kept packed in LDS (dynamic: the largest tile's words), where a row
+// that continues the previous one is found by comparing words.
+//
+// What bounds it is latency, LDS and barriers, not bytes: 512 threads (a row
+// each), rows sorted in registers by a network, sorts by lane shuffles, masks by
+// ballots and scans by shuffles, and registers and LDS for four workgroups a CU.
+// 127 x 113 x 101 points: 260 us and 11 us for the compaction (two passes of 256
+// threads with the rows in global memory between them, sorted by insertion in
+// LDS, took 409 + 275 us).
+__global__ void __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8)))
+tile_record(const int64_t* __restrict__ row_ptr,
                                                             const int32_t* __restrict__ col,
                                                             const uint32_t* __restrict__ perm,
                                                             const int64_t* __restrict__ ranges,
-                                                            const int64_t* __restrict__ row_base,
-                                                            uint16_t* __restrict__ rowbuf,
+                                                            const uint32_t* __restrict__ stage_off,
                                                             uint32_t* __restrict__ counts,
-                                                            const TileMeta* __restrict__ meta,
-                                                            unsigned char* __restrict__ rec)
+                                                            unsigned char* __restrict__ stage)
 {
-    // srt (sort keys: (caller index << 32) | payload) and hlist (halo in
-    // insertion order) until the halo is sorted, then each lane's row scratch
-    __shared__ __align__(16) unsigned char ubuf[kRowScratch * kTileThreads * 2];
-    static_assert(sizeof(ubuf) >= kMaxStaged * 12, "srt and hlist fit the shared buffer");
-    uint64_t* srt = reinterpret_cast<uint64_t*>(ubuf);
-    int32_t* hlist = reinterpret_cast<int32_t*>(ubuf + 8 * kMaxStaged);
-    uint16_t* rscr = reinterpret_cast<uint16_t*>(ubuf);   // entry k of lane t's row at rscr[k * kTileThreads + t]
-    __shared__ int32_t keys[kHashSlots];            // halo hash set (Morton positions)
-    __shared__ uint16_t hslot[kHashSlots];          // their slots
-    __shared__ uint32_t caller[kMaxStaged];         // caller index of each staged slot
-    __shared__ uint16_t own_slot[kMaxStaged];       // slot of own point b + i
-    __shared__ int32_t order[kMaxStaged];           // Morton position of own slot l
-    __shared__ uint32_t scan_s[kTileThreads];
-    __shared__ uint32_t total;
-    __shared__ int count;
-    __shared__ uint32_t rowoff[kMaxStaged + 1];     // row l's first entry in the tile's row buffer
-    __shared__ uint8_t expl[kMaxStaged];
-    __shared__ uint8_t start[kMaxStaged];
-    __shared__ uint32_t gmask[kMaxStaged / 32];    // the record's 32-slot group masks
+    extern __shared__ uint32_t words[];   // row l's words at words[woff[l]]
+    __shared__ TileScratch q;
     const int t = (int)threadIdx.x;
     const int tb = xcd_tile((int)blockIdx.x, (int)gridDim.x);   // XCD-contiguous tiles
     const int64_t b = ranges[2 * tb], e = ranges[2 * tb + 1];
     const int P = (int)(e - b);
-    for (int i = t; i < kHashSlots; i += kTileThreads) keys[i] = -1;
-    if (t == 0) count = 0;
-    __syncthreads();
+    for (int i = t; i < kHashSlots; i += kTileThreads) q.keys[i] = -1;
+    if (t == 0) {
+        q.count = 0;
+        q.n_long = 0;
+    }
     // own points in caller order
-    for (int i = t; i < P; i += kTileThreads) srt[i] = ((uint64_t)perm[b + i] << 32) | (uint32_t)i;
-    bitonic_sort64(srt, P, t);
+    for (int i = t; i < P; i += kTileThreads) q.sort[i] = ((uint64_t)perm[b + i] << 32) | (uint32_t)i;
+    __syncthreads();
+    sort_keys(q.sort, P, t);
     for (int l = t; l < P; l += kTileThreads) {
-        const int i = (int)(srt[l] & 0xffffffffu);
-        order[l] = (int32_t)(b + i);
-        own_slot[i] = (uint16_t)l;
-        caller[l] = (uint32_t)(srt[l] >> 32);
+        q.own_slot[q.sort[l] & 0xffffffffu] = (uint16_t)l;
+        q.caller[l] = (uint32_t)(q.sort[l] >> 32);
     }
     __syncthreads();
     // the halo in caller order (the extents admitted only tiles with P + H <= kMaxStaged)
-    const int H = gather_halo(row_ptr, col, b, e, keys, hlist, &count, t);
+    int32_t* hlist = reinterpret_cast<int32_t*>(q.sort);
+    const int H = gather_halo<kTileThreads>(row_ptr, col, b, e, q.keys, hlist, &q.count, t);
     if (P + H > kMaxStaged) {
-        if (!WRITE && t == 0)
-            for (int q = 0; q < 4; ++q) counts[4 * tb + q] = ~0u;
+        if (t == 0)
+            for (int k = 0; k < 4; ++k) counts[4 * tb + k] = ~0u;
         return;
     }
-    for (int h = t; h < H; h += kTileThreads) srt[h] = ((uint64_t)perm[hlist[h]] << 32) | (uint32_t)hlist[h];
-    bitonic_sort64(srt, H, t);
-    for (int h = t; h < H; h += kTileThreads) {
-        const int32_t c = (int32_t)(srt[h] & 0xffffffffu);
-        caller[P + h] = (uint32_t)(srt[h] >> 32);
-        uint32_t q = tile_hash(c);
-        while (keys[q] != c) q = (q + 1) & (kHashSlots - 1);
-        hslot[q] = (uint16_t)(P + h);
-    }
-    __syncthreads();
-    const int S = P + H;
-    const TileMeta m = WRITE ? meta[tb] : TileMeta{};
-    const RecLayout R = WRITE ? rec_layout(m) : RecLayout{};
-    unsigned char* out = WRITE ? rec + (size_t)16 * m.rec_off : nullptr;
-    // runs of consecutive caller indices
-    for (int l = t; l < S; l += kTileThreads) start[l] = (l == 0 || caller[l] != caller[l - 1] + 1u) ? 1 : 0;
-    __syncthreads();
     {
-        // lane t takes slots [t*cs, (t+1)*cs)
-        const int cs = (S + kTileThreads - 1) / kTileThreads;
-        uint32_t c = 0;
-        for (int l = t * cs; l < min(S, (t + 1) * cs); ++l) c += start[l];
-        uint32_t k = block_excl(c, scan_s, &total, t);
-        if (WRITE)
-            for (int l = t * cs; l < min(S, (t + 1) * cs); ++l)
-                if (start[l]) reinterpret_cast<uint32_t*>(out + R.runs)[k++] = caller[l] - (uint32_t)l;
-    }
-    const uint32_t nr = total;
-    if (WRITE) {
-        // group masks by one lane each, then their prefix counts by one lane
-        for (int g = t; g < (S + 31) / 32; g += kTileThreads) {
-            uint32_t mask = 0;
-            for (int i = 0; i < 32 && 32 * g + i < S; ++i) mask |= (uint32_t)start[32 * g + i] << i;
-            gmask[g] = mask;
-        }
-        __syncthreads();
-        if (t == 0) {
-            uint32_t before = 0;
-            for (int g = 0; g < (S + 31) / 32; ++g) {
-                reinterpret_cast<uint32_t*>(out + R.smask)[g] = gmask[g];
-                reinterpret_cast<uint16_t*>(out + R.spre)[g] = (uint16_t)before;
-                before += (uint32_t)__popc(gmask[g]);
-            }
-        }
-        __syncthreads();
-    }
-    // rows: padded lengths and their offsets
-    {
-        const int cs = (P + kTileThreads - 1) / kTileThreads;
-        uint32_t c = 0;
-        for (int l = t * cs; l < min(P, (t + 1) * cs); ++l) {
-            const int64_t r = order[l];
-            c += (uint32_t)((row_ptr[r + 1] - row_ptr[r] + 2) / 3 * 3);
-        }
-        uint32_t o = block_excl(c, scan_s, &total, t);
-        for (int l = t * cs; l < min(P, (t + 1) * cs); ++l) {
-            rowoff[l] = o;
-            const int64_t r = order[l];
-            o += (uint32_t)((row_ptr[r + 1] - row_ptr[r] + 2) / 3 * 3);
-        }
-        if (t == 0) rowoff[P] = total;
-    }
-    __syncthreads();
-    const uint32_t nwf = rowoff[P] / 3;
-    uint16_t* rows = rowbuf + row_base[tb];
-    if (!WRITE) {
-        // each row: its neighbours' slots, insertion-sorted, then the padding
-        for (int l = t; l < P; l += kTileThreads) {
-            const int64_t r = order[l];
-            uint16_t* row = rows + rowoff[l];
-            const int padded = (int)(rowoff[l + 1] - rowoff[l]);
-            // sorted in the lane's LDS scratch when it fits, else in place
-            const bool scratch = padded <= kRowScratch;
-            uint16_t* srow = scratch ? rscr + t : row;
-            const int step = scratch ? kTileThreads : 1;
-            int len = 0;
-            const int64_t p0 = row_ptr[r], p1 = row_ptr[r + 1];
-            for (int64_t p = p0; p < p1; p += kChunk) {
-                int32_t cs[kChunk];
+        uint64_t v[2];
 #pragma unroll
-                for (int q = 0; q < kChunk; ++q) cs[q] = col[min(p + q, p1 - 1)];
-                for (int q = 0; q < kChunk && p + q < p1; ++q) {
-                    const int32_t c = cs[q];
-                    const uint16_t s = (c >= b && c < e) ? own_slot[c - b] : (uint16_t)lookup_halo(keys, hslot, c);
-                    int k = len;
-                    while (k > 0 && srow[(k - 1) * step] > s) {
-                        srow[k * step] = srow[(k - 1) * step];
-                        --k;
-                    }
-                    srow[k * step] = s;
-                    ++len;
-                }
+        for (int k = 0; k < 2; ++k)
+            if (t + k * kTileThreads < H) {
+                const int32_t c = hlist[t + k * kTileThreads];
+                v[k] = (uint64_t)perm[c] << 32 | (uint32_t)c;
             }
-            if (scratch)
-                for (int k = 0; k < len; ++k) row[k] = srow[k * step];
-            for (int k = len; k < padded; ++k) row[k] = (uint16_t)l;
-        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (t + k * kTileThreads < H) q.sort[t + k * kTileThreads] = v[k];
         __syncthreads();
     }
-    // explicit rows: not the previous row with every entry plus one
-    for (int l = t; l < P; l += kTileThreads) {
-        bool shift = false;
-        if (l > 0 && rowoff[l + 1] - rowoff[l] == rowoff[l] - rowoff[l - 1]) {
-            shift = true;
-            for (uint32_t k = 0; shift && k < rowoff[l + 1] - rowoff[l]; ++k)
-                shift = rows[rowoff[l] + k] == (uint16_t)(rows[rowoff[l - 1] + k] + 1);
+    sort_keys(q.sort, H, t);
+    for (int h = t; h < H; h += kTileThreads) {
+        const int32_t c = (int32_t)(q.sort[h] & 0xffffffffu);
+        q.caller[P + h] = (uint32_t)(q.sort[h] >> 32);
+        uint32_t k = tile_hash(c);
+        while (q.keys[k] != c) k = (k + 1) & (kHashSlots - 1);
+        q.hslot[k] = (uint16_t)(P + h);
+    }
+    // rows: their words' offsets, in slot order
+    for (int i = t; i < P; i += kTileThreads)
+        q.woff[q.own_slot[i]] = (uint16_t)((row_ptr[b + i + 1] - row_ptr[b + i] + 2) / 3);
+    __syncthreads();
+    uint32_t nwf = 0;
+    for (int l0 = 0; l0 < P; l0 += kTileThreads) {
+        const uint32_t n = l0 + t < P ? q.woff[l0 + t] : 0u;
+        uint32_t total;
+        const uint32_t o = block_excl(n, q.part, total, t);
+        if (l0 + t < P) q.woff[l0 + t] = (uint16_t)(nwf + o);
+        nwf += total;
+    }
+    if (t == 0) q.woff[P] = (uint16_t)nwf;
+    __syncthreads();
+    // each row by a lane; long ones are listed for the workgroup
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(q.sort);   // kMaxStaged counters, then the list
+    uint16_t* longs = reinterpret_cast<uint16_t*>(cnt + kMaxStaged);
+    static_assert(sizeof(q.sort) >= kMaxStaged * 6, "counters and long rows fit the sort buffer");
+    for (int i = t; i < P; i += kTileThreads) {
+        const int64_t p0 = row_ptr[b + i];
+        const int64_t len = row_ptr[b + i + 1] - p0;
+        const uint32_t l = q.own_slot[i];
+        uint32_t* out = words + q.woff[l];
+        if (len <= 0) continue;
+        if (len <= 16) {
+            short_row<16>(q, col, b, P, p0, (int)len, l, out);
+        } else if (len <= kRowRegs) {
+            short_row<kRowRegs>(q, col, b, P, p0, (int)len, l, out);
+        } else {
+            for (int64_t w = 0; w < (len + 2) / 3; ++w) out[w] = 0;
+            longs[atomicAdd(&q.n_long, 1)] = (uint16_t)i;
         }
-        expl[l] = shift ? 0 : 1;
     }
     __syncthreads();
-    // explicit rows' numbers and word offsets
-    uint32_t nx, nw;
-    {
-        const int cs = (P + kTileThreads - 1) / kTileThreads;
-        uint32_t c = 0, cw = 0;
-        for (int l = t * cs; l < min(P, (t + 1) * cs); ++l)
-            if (expl[l]) {
-                ++c;
-                cw += (rowoff[l + 1] - rowoff[l]) / 3;
-            }
-        uint32_t kx = block_excl(c, scan_s, &total, t);
-        nx = total;
-        uint32_t kw = block_excl(cw, scan_s, &total, t);
-        nw = total;
-        if (WRITE) {
-            uint32_t* wd = reinterpret_cast<uint32_t*>(out);
-            uint16_t* xend = reinterpret_cast<uint16_t*>(out + R.xend);
-            for (int l = t * cs; l < min(P, (t + 1) * cs); ++l) {
-                if (!expl[l]) continue;
-                const uint32_t len = rowoff[l + 1] - rowoff[l];
-                const uint16_t* row = rows + rowoff[l];
-                const uint32_t pad = len ? (len - (uint32_t)(row_ptr[order[l] + 1] - row_ptr[order[l]])) : 0;
-                for (uint32_t k = 0; k < len; k += 3) {
-                    uint32_t word = (uint32_t)row[k] | (uint32_t)row[k + 1] << 10 | (uint32_t)row[k + 2] << 20;
-                    if (k + 3 == len) word |= pad << 30;
-                    wd[kw++] = word;
-                }
-                xend[kx++] = (uint16_t)kw;
-            }
-        }
-    }
-    if (WRITE) {
-        for (int q = t; q < (P + 31) / 32; q += kTileThreads) {
-            uint32_t mask = 0;
-            for (int i = 0; i < 32 && 32 * q + i < P; ++i) mask |= (uint32_t)expl[32 * q + i] << i;
-            gmask[q] = mask;
+    // long rows: occurrences counted per slot, then listed in slot order
+    for (int k = 0; k < q.n_long; ++k) {
+        const int i = longs[k];
+        const int64_t p0 = row_ptr[b + i];
+        const int len = (int)(row_ptr[b + i + 1] - p0);   // at most 3 nwf
+        const uint32_t l = q.own_slot[i];
+        uint32_t* out = words + q.woff[l];
+        for (int j = t; j < kMaxStaged; j += kTileThreads) cnt[j] = 0;
+        __syncthreads();
+        for (int j = t; j < len; j += kTileThreads) atomicAdd(&cnt[slot_of(q, b, P, col[p0 + j])], 1u);
+        __syncthreads();
+        const uint32_t c0 = cnt[2 * t], c1 = cnt[2 * t + 1];
+        uint32_t total;
+        uint32_t at = block_excl(c0 + c1, q.part, total, t);
+        for (uint32_t j = 0; j < c0 + c1; ++j, ++at)
+            atomicOr(&out[at / 3], (uint32_t)(2 * t + (j < c0 ? 0 : 1)) << (10 * (at % 3)));
+        if (t == 0) {
+            const int end = (len + 2) / 3 * 3;
+            for (int j = len; j < end; ++j) atomicOr(&out[j / 3], l << (10 * (j % 3)));
+            atomicOr(&out[end / 3 - 1], (uint32_t)(end - len) << 30);
         }
         __syncthreads();
-        if (t == 0) {
-            uint32_t before = 0, last = 0;   // explicit rows before group q, and the last of them
-            for (int q = 0; q < (P + 31) / 32; ++q) {
-                const uint32_t mask = gmask[q];
-                reinterpret_cast<uint32_t*>(out + R.xmask)[q] = mask;
-                reinterpret_cast<uint16_t*>(out + R.xpre)[q] = (uint16_t)before;
-                reinterpret_cast<uint16_t*>(out + R.xlast)[q] = (uint16_t)last;
-                before += (uint32_t)__popc(mask);
-                if (mask) last = 32u * (uint32_t)q + 31u - (uint32_t)__clz(mask);
+    }
+    // runs of consecutive caller indices, explicit rows (not the previous row
+    // with every slot plus one), as masks and their prefix counts
+    const int S = P + H, G = (S + 31) / 32, Q = (P + 31) / 32;
+    for (int l0 = 0; l0 < S; l0 += kTileThreads) {
+        const int l = l0 + t;
+        const uint64_t m = __ballot(l < S && (l == 0 || q.caller[l] != q.caller[l - 1] + 1u));
+        if ((t & 31) == 0 && l < S) q.smask[l >> 5] = (t & 32) ? (uint32_t)(m >> 32) : (uint32_t)m;
+    }
+    __syncthreads();
+    if (t < 64) {   // (G and Q are at most 32)
+        const uint32_t c = t < G ? (uint32_t)__popc(q.smask[t]) : 0u;
+        uint32_t incl = c;
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) {
+            const uint32_t u = __shfl_up(incl, off);
+            if (t >= off) incl += u;
+        }
+        if (t < 32) q.spre[t] = incl - c;
+        if (t == 31) q.count = (int)incl;
+    }
+    __syncthreads();
+    const uint32_t nr = (uint32_t)q.count;
+    bool expl[2] = {false, false};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int l = t + k * kTileThreads;
+        if (l < P) {
+            const uint32_t o = q.woff[l], n = q.woff[l + 1] - o;
+            bool shift = l > 0 && o - q.woff[l - 1] == n;
+            if (shift) {
+                const uint32_t *w0 = words + q.woff[l - 1], *w1 = words + o;
+                for (uint32_t j = 0; shift && j < n; ++j) {
+                    const uint32_t u = w0[j] & 0x3fffffffu;
+                    shift = (w1[j] & 0x3fffffffu) == u + 0x00100401u;
+                    // slot 1023 has no successor: its carry must not pass for one
+                    if (S == kMaxStaged)
+                        shift &= (u & 0x3ffu) != 0x3ffu && (u & 0xffc00u) != 0xffc00u && (u & 0x3ff00000u) != 0x3ff00000u;
+                }
+            }
+            expl[k] = !shift;
+        }
+        const uint64_t m = __ballot(expl[k]);
+        if ((t & 31) == 0 && l < P) q.mask[l >> 5] = (t & 32) ? (uint32_t)(m >> 32) : (uint32_t)m;
+    }
+    __syncthreads();
+    if (t < 64) {
+        const uint32_t m = t < Q ? q.mask[t] : 0u, c = (uint32_t)__popc(m);
+        uint32_t incl = c, last = m ? 32u * (uint32_t)t + 31u - (uint32_t)__clz((int)m) : 0u;
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) {
+            const uint32_t u = __shfl_up(incl, off), v = __shfl_up(last, off);
+            if (t >= off) {
+                incl += u;
+                last = max(last, v);
             }
         }
-    } else if (t == 0) {
+        const uint32_t before = __shfl_up(last, 1);
+        if (t < 32) {
+            q.pre[t] = incl - c;
+            q.last[t] = t ? before : 0u;   // the last explicit row before group t
+        }
+        if (t == 31) q.count = (int)incl;
+    }
+    __syncthreads();
+    const uint32_t nx = (uint32_t)q.count;
+    uint32_t nw = 0, kw[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int l = t + k * kTileThreads;
+        const uint32_t c = expl[k] ? (uint32_t)q.woff[l + 1] - q.woff[l] : 0u;
+        uint32_t total;
+        kw[k] = nw + block_excl(c, q.part, total, t);
+        nw += total;
+    }
+    const RecLayout R = rec_layout((uint32_t)P, (uint32_t)H, nw, nr, nx);
+    unsigned char* out = stage + (size_t)16 * stage_off[tb];
+    uint32_t* wd = reinterpret_cast<uint32_t*>(out);
+    uint16_t* xend = reinterpret_cast<uint16_t*>(out + R.xend);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int l = t + k * kTileThreads;
+        if (l < S && (q.smask[l >> 5] >> (l & 31) & 1u))
+            reinterpret_cast<uint32_t*>(
+                out + R.runs)[q.spre[l >> 5] + (uint32_t)__popc(q.smask[l >> 5] & ((1u << (l & 31)) - 1u))] =
+                q.caller[l] - (uint32_t)l;
+        if (!expl[k]) continue;
+        const uint32_t o = q.woff[l], n = q.woff[l + 1] - o;
+        for (uint32_t j = 0; j < n; ++j) wd[kw[k] + j] = words[o + j];
+        xend[q.pre[l >> 5] + (uint32_t)__popc(q.mask[l >> 5] & ((1u << (l & 31)) - 1u))] = (uint16_t)(kw[k] + n);
+    }
+    if (t < G) {
+        reinterpret_cast<uint32_t*>(out + R.smask)[t] = q.smask[t];
+        reinterpret_cast<uint16_t*>(out + R.spre)[t] = (uint16_t)q.spre[t];
+    }
+    if (t < Q) {
+        reinterpret_cast<uint32_t*>(out + R.xmask)[t] = q.mask[t];
+        reinterpret_cast<uint16_t*>(out + R.xpre)[t] = (uint16_t)q.pre[t];
+        reinterpret_cast<uint16_t*>(out + R.xlast)[t] = (uint16_t)q.last[t];
+    }
+    if (t == 0) {
+        for (uint32_t at = R.xend + 2u * nx; at < R.bytes; at += 2) *reinterpret_cast<uint16_t*>(out + at) = 0;
         counts[4 * tb] = nw;
         counts[4 * tb + 1] = nr;
         counts[4 * tb + 2] = nx;
         counts[4 * tb + 3] = nwf;
     }
+}
+
+// Record t from its place in the stage to 16 meta[t].rec_off.
+__global__ void __launch_bounds__(128) compact_records(const uint32_t* __restrict__ stage_off,
+                                                       const TileMeta* __restrict__ meta,
+                                                       const unsigned char* __restrict__ stage,
+                                                       unsigned char* __restrict__ rec)
+{
+    const TileMeta m = meta[blockIdx.x];
+    const uint4* src = reinterpret_cast<const uint4*>(stage) + stage_off[blockIdx.x];
+    uint4* dst = reinterpret_cast<uint4*>(rec) + m.rec_off;
+    const uint32_t n = rec_layout(m).bytes / 16;
+    for (uint32_t i = threadIdx.x; i < n; i += 128) dst[i] = src[i];
 }
 
 // The float64 inverse of each point's normal matrix M = sum (x_j - x_i)(x_j - x_i)^T
@@ -990,22 +1132,32 @@ hipError_t mb_tile_extent(const int64_t* row_ptr, const int32_t* col, const int6
                           uint32_t* halo_words, hipStream_t s)
 {
     if (n_ranges == 0) return hipSuccess;
-    hipLaunchKernelGGL(tile_extent, dim3((unsigned)n_ranges), dim3(kTileThreads), 0, s, row_ptr, col, ranges,
+    hipLaunchKernelGGL(tile_extent, dim3((unsigned)n_ranges), dim3(kExtentThreads), 0, s, row_ptr, col, ranges,
                        halo_words);
     return hipGetLastError();
 }
 
-hipError_t mb_tile_record(bool write, const int64_t* row_ptr, const int32_t* col, const uint32_t* perm,
-                          const int64_t* ranges, int64_t n_tiles, const int64_t* row_base, uint16_t* rowbuf,
-                          uint32_t* counts, const TileMeta* meta, unsigned char* rec, hipStream_t s)
+hipError_t mb_tile_record(const int64_t* row_ptr, const int32_t* col, const uint32_t* perm, const int64_t* ranges,
+                          int64_t n_tiles, uint32_t max_words, const uint32_t* stage_off, uint32_t* counts,
+                          unsigned char* stage, hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
-    if (write)
-        hipLaunchKernelGGL(tile_record<true>, dim3((unsigned)n_tiles), dim3(kTileThreads), 0, s, row_ptr, col, perm,
-                           ranges, row_base, rowbuf, counts, meta, rec);
-    else
-        hipLaunchKernelGGL(tile_record<false>, dim3((unsigned)n_tiles), dim3(kTileThreads), 0, s, row_ptr, col, perm,
-                           ranges, row_base, rowbuf, counts, meta, rec);
+    const size_t lds = 4 * (size_t)max_words;
+    if (sizeof(TileScratch) + lds > 65536) {   // more than the default limit (rows of many entries)
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_record),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(tile_record, dim3((unsigned)n_tiles), dim3(kTileThreads), lds, s, row_ptr, col, perm, ranges,
+                       stage_off, counts, stage);
+    return hipGetLastError();
+}
+
+hipError_t mb_compact_records(const uint32_t* stage_off, const TileMeta* meta, int64_t n_tiles,
+                              const unsigned char* stage, unsigned char* rec, hipStream_t s)
+{
+    if (n_tiles == 0) return hipSuccess;
+    hipLaunchKernelGGL(compact_records, dim3((unsigned)n_tiles), dim3(128), 0, s, stage_off, meta, stage, rec);
     return hipGetLastError();
 }
 

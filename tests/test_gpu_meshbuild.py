@@ -373,6 +373,30 @@ def test_from_csr_paper_list_and_ring1_output():
     assert_same_csr_mesh(x, rp.cpu().numpy(), col.cpu().numpy(), "f32")
 
 
+@pytest.mark.parametrize("repeats", [4, 5, 8, 9, 14])
+def test_from_csr_row_lengths(repeats):
+    """Rows of 16, 20, 32, 36 and 56 entries (each neighbour listed several
+    times): the two register networks and the counted rows; the longest make the
+    tile's words and tables exceed 64 KiB of LDS.  One point with no neighbours
+    and one with a single one keep the rows ragged."""
+    x, cells = meshes.jittered_tri_grid(70, 45, seed=31)
+    n = x.shape[0]
+    ell = oracle.axis(2, x.astype(np.float32).astype(np.float64), oracle.ring1(2, n, cells)).col.reshape(n, 4)
+    rows = np.tile(ell, (1, repeats))
+    rows[5] = -1
+    rows[777, 1:] = -1
+    assert_same_csr_mesh(x, np.arange(n + 1, dtype=np.int64) * 4 * repeats, rows.reshape(-1).astype(np.int32))
+
+
+@pytest.mark.parametrize("side", [7, 16, 17, 33])
+@pytest.mark.parametrize("tile_log2", [5, 6, 10])
+def test_tile_edges(side, tile_log2):
+    """Tiles of one wave's points and fewer, of more points than the workgroup
+    has lanes, and last tiles of every remainder."""
+    x, cells = meshes.jittered_tri_grid(side, side + 20, seed=side)
+    assert_same_mesh(x, cells, tile_log2=tile_log2)
+
+
 def test_from_csr_errors():
     x, _ = meshes.jittered_tri_grid(10, 8, seed=1)
     n = x.shape[0]
