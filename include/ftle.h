@@ -81,7 +81,8 @@ enum {
 };
 /* Points per tile (one workgroup's share): FTLE_TILE(k) asks for 2^k points,
  * 5 <= k <= 11; 0 selects the default, 512.  A tile is halved until its own
- * and halo points fit 1024 staged slots and 64 KiB of LDS. */
+ * and halo points fit 1024 staged slots and 64 KiB of LDS (96 KiB in 3D
+ * float64). */
 #define FTLE_TILE(k) ((unsigned)(k) << 8)
 
 /*
@@ -349,7 +350,8 @@ ftle_status ftle_mesh_get_tiles(ftle_mesh_t mesh, int adjoint, int64_t* n_tiles,
  * Threads per workgroup of this mesh's forward (and forward+tape) kernel and
  * of its adjoint gather kernel: each 128, 256 or 512 (0 keeps the current
  * value; the default is 256 in 2D and 512 in 3D).  A workgroup always
- * processes one whole tile.
+ * processes one whole tile; where all tiles of a mesh hold at most half as
+ * many points, launches use fewer threads.
  * Errors: INVALID_ARG for a NULL mesh or another block size.
  */
 ftle_status ftle_mesh_set_blocks(ftle_mesh_t mesh, int fwd_block, int adjoint_block);

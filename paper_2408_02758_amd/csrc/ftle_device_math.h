@@ -32,8 +32,6 @@ __device__ inline float drcp(float v) { return __builtin_amdgcn_rcpf(v); }
 __device__ inline double drcp(double v) { return 1.0 / v; }
 __device__ inline float dsqrt(float v) { return __builtin_amdgcn_sqrtf(v); }
 __device__ inline double dsqrt(double v) { return sqrt(v); }
-__device__ inline double dacos(double v) { return acos(v); }
-__device__ inline double dcos(double v) { return cos(v); }
 __device__ inline float dfma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ inline double dfma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ inline float dmin(float a, float b) { return fminf(a, b); }
@@ -93,12 +91,32 @@ __device__ inline void cubic_qpr(T c00, T c01, T c02, T c11, T c12, T c22, T& q,
     r = dmin(dmax(r, T(-1)), T(1));
 }
 
-__device__ inline double lam_max3_trig(double c00, double c01, double c02, double c11, double c12, double c22,
+// double: c = cos((2/3) acos(s)), s = sqrt((1 + r)/2), as a polynomial in
+// u = s - 1/2 on [0, 1] (csrc/gen_eig_poly.py; dropped terms 3.7e-18, error in
+// Horner form 1.1e-16): half the instructions of the library's acos and cos.
+// Its coefficients are read (scalar loads) where they are used, through a
+// pointer the compiler cannot see behind: as literals it keeps them in vector
+// registers across the loop over a tile's rows, and the 3D float64 forward
+// then no longer fits the 128 registers of four waves per SIMD.
+__constant__ double kEigPoly[20] = {
+    0.766044443118978, 0.49481813264570607, -0.062036753745945694, 0.019730822520698705,
+    -0.008065995058000701, 0.003725614493912388, -0.001850875932177013, 0.0009652580660097717,
+    -0.0005211824563454097, 0.00028884529336952754, -0.00016337446432180538, 9.392215760218694e-05,
+    -5.466191327612715e-05, 3.219016325584648e-05, -1.9464458091489548e-05, 1.1714871704272548e-05,
+    -5.982240282331103e-06, 3.543752785969229e-06, -4.217695979632236e-06, 2.664713851949588e-06};
+
+__device__ inline double lam_max3_poly(double c00, double c01, double c02, double c11, double c12, double c22,
                                        double& r)
 {
     double q, p;
     cubic_qpr<double>(c00, c01, c02, c11, c12, c22, q, p, r);
-    return q + 2.0 * p * dcos(dacos(r) * (1.0 / 3.0));
+    const double u = sqrt(0.5 * (1.0 + r)) - 0.5;
+    const __attribute__((address_space(4))) double* k = (const __attribute__((address_space(4))) double*)kEigPoly;
+    asm volatile("" : "+s"(k));
+    double c = k[19];
+#pragma unroll
+    for (int i = 18; i >= 0; --i) c = dfma(c, u, k[i]);
+    return dfma(2.0 * p, c, q);
 }
 
 // float: c = cos(acos(r)/3) = P7(s), s = sqrt((1 + r)/2), with P7 a degree-7
@@ -121,7 +139,7 @@ __device__ inline float lam_max3_poly(float c00, float c01, float c02, float c11
 }
 
 // The float64 recompute of lambda_max from a float32 Jacobian: C = J^T J and
-// the trigonometric formula in double.  Out of line: it runs for a handful of
+// the closed form in double.  Out of line: it runs for a handful of
 // points per launch and would otherwise raise the register budget of every
 // lane.
 __device__ __noinline__ float lam_max3_f64_from_J(float j00, float j01, float j02, float j10, float j11,
@@ -130,7 +148,7 @@ __device__ __noinline__ float lam_max3_f64_from_J(float j00, float j01, float j0
     const double e00 = j00, e01 = j01, e02 = j02, e10 = j10, e11 = j11, e12 = j12;
     const double e20 = j20, e21 = j21, e22 = j22;
     double rd;
-    const double lamd = lam_max3_trig(e00 * e00 + e10 * e10 + e20 * e20, e00 * e01 + e10 * e11 + e20 * e21,
+    const double lamd = lam_max3_poly(e00 * e00 + e10 * e10 + e20 * e20, e00 * e01 + e10 * e11 + e20 * e21,
                                       e00 * e02 + e10 * e12 + e20 * e22, e01 * e01 + e11 * e11 + e21 * e21,
                                       e01 * e02 + e11 * e12 + e21 * e22, e02 * e02 + e12 * e12 + e22 * e22, rd);
     return (float)lamd;

@@ -111,15 +111,13 @@ __device__ inline T ell_epilogue3(const T (&m)[6], const T (&b)[9], T inv2T, flo
     const T c11 = j[1] * j[1] + j[4] * j[4] + j[7] * j[7];
     const T c12 = j[1] * j[2] + j[4] * j[5] + j[7] * j[8];
     const T c22 = j[2] * j[2] + j[5] * j[5] + j[8] * j[8];
-    T r, lam;
+    T r;
+    T lam = lam_max3_poly(c00, c01, c02, c11, c12, c22, r);
     if constexpr (sizeof(T) == 4) {
-        lam = lam_max3_poly(c00, c01, c02, c11, c12, c22, r);
         if (ok && (r + 1.0f < eig_tau)) {   // top pair nearly equal: float64 from J
             lam = lam_max3_f64_from_J(j[0], j[1], j[2], j[3], j[4], j[5], j[6], j[7], j[8]);
             ++redone;
         }
-    } else {
-        lam = lam_max3_trig(c00, c01, c02, c11, c12, c22, r);
     }
     return ok ? log_scaled(lam, inv2T) : quiet_nan<T>();
 }

@@ -201,6 +201,14 @@ struct TileSet {
     void* d_rec = nullptr;
     void* d_minv = nullptr;   // 3D forward tile set: inverse normal matrices (caller order)
 
+    // Threads a workgroup launches with, `block` the mesh's setting: halved
+    // while half of it still covers the largest tile's points (the rest would
+    // only help stage).
+    int threads(int block) const
+    {
+        while (block > 128 && block / 2 >= max_P) block /= 2;
+        return block;
+    }
     DevTiles dev() const
     {
         DevTiles d;
@@ -244,6 +252,8 @@ struct ftle_mesh_s {
     bool f64() const { return dtype == FTLE_F64; }
     size_t elem() const { return f64() ? 8 : 4; }
     const TileSet& adj_tiles() const { return symmetric ? fwd : bwd; }
+    int fwd_threads() const { return fwd.threads(fwd_block); }
+    int bwd_threads() const { return adj_tiles().threads(bwd_block); }
 };
 
 namespace {
@@ -442,8 +452,7 @@ bool tile_fits(int dim, bool f64, int64_t P, int64_t H, int64_t nw)
     if (P + H > kMaxStaged || nw > kMaxTileWords) return false;
     const RecLayout r = rec_layout((uint32_t)P, (uint32_t)H, (uint32_t)nw, (uint32_t)(P + H), (uint32_t)P);
     const int S = (int)(P + H);
-    if (dim == 3 && S > bwd3_capacity(f64)) return false;
-    return std::max(fwd_points_bytes(dim, f64, S), bwd_points_bytes(dim, f64, S)) + r.bytes <= kLdsBudget;
+    return std::max(fwd_points_bytes(dim, f64, S), bwd_points_bytes(dim, f64, S)) + r.bytes <= lds_budget(dim, f64);
 }
 
 // The record of one tile (layout in ftle_internal.h): own points [b, e) of
@@ -1764,7 +1773,7 @@ ftle_status ftle_forward(ftle_mesh_t mesh, const void* flow, ftle_dtype dtype, d
         need_device(mesh);
         DeviceScope ds(mesh->device);
         check_hip(launch_forward(mesh->dim, mesh->f64(), mesh->fwd.dev(), mesh->d_x, flow, 0.5 / std::fabs(T),
-                                 out, nullptr, false, mesh->n, eig_tau(), mesh->d_hits, mesh->fwd_block,
+                                 out, nullptr, false, mesh->n, eig_tau(), mesh->d_hits, mesh->fwd_threads(),
                                  static_cast<hipStream_t>(stream)),
                   "forward launch");
     });
@@ -1801,7 +1810,7 @@ ftle_status ftle_forward_f16(ftle_mesh_t mesh, const void* delta, double T, void
         need_device(mesh);
         DeviceScope ds(mesh->device);
         check_hip(launch_forward_f16(mesh->fwd.dev(), mesh->d_x, delta, 0.5 / std::fabs(T), out, mesh->n, eig_tau(),
-                                     mesh->d_hits, mesh->fwd_block, static_cast<hipStream_t>(stream)),
+                                     mesh->d_hits, mesh->fwd_threads(), static_cast<hipStream_t>(stream)),
                   "forward (half-precision flow) launch");
     });
 }
@@ -1826,7 +1835,7 @@ ftle_status ftle_forward_tape(ftle_mesh_t mesh, const void* flow, ftle_dtype dty
         need_device(mesh);
         DeviceScope ds(mesh->device);
         check_hip(launch_forward(mesh->dim, mesh->f64(), mesh->fwd.dev(), mesh->d_x, flow, 0.5 / std::fabs(T),
-                                 out, tape, !mesh->symmetric, mesh->n, eig_tau(), mesh->d_hits, mesh->fwd_block,
+                                 out, tape, !mesh->symmetric, mesh->n, eig_tau(), mesh->d_hits, mesh->fwd_threads(),
                                  static_cast<hipStream_t>(stream)),
                   "forward+tape launch");
     });
@@ -1842,7 +1851,7 @@ ftle_status ftle_backward_tape(ftle_mesh_t mesh, const void* tape, ftle_dtype dt
         need_device(mesh);
         DeviceScope ds(mesh->device);
         check_hip(launch_backward_gather(mesh->dim, mesh->f64(), mesh->adj_tiles().dev(), mesh->d_x, tape,
-                                         !mesh->symmetric, mesh->n, grad_ftle, grad_flow, mesh->bwd_block,
+                                         !mesh->symmetric, mesh->n, grad_ftle, grad_flow, mesh->bwd_threads(),
                                          static_cast<hipStream_t>(stream)),
                   "adjoint launch");
     });
@@ -1869,10 +1878,10 @@ ftle_status ftle_backward(ftle_mesh_t mesh, const void* flow, ftle_dtype dtype, 
         }
         check_hip(launch_forward(mesh->dim, mesh->f64(), mesh->fwd.dev(), mesh->d_x, flow, 0.5 / std::fabs(T),
                                  nullptr, mesh->d_work, !mesh->symmetric, mesh->n, eig_tau(), mesh->d_hits,
-                                 mesh->fwd_block, s),
+                                 mesh->fwd_threads(), s),
                   "adjoint tape launch");
         check_hip(launch_backward_gather(mesh->dim, mesh->f64(), mesh->adj_tiles().dev(), mesh->d_x, mesh->d_work,
-                                         !mesh->symmetric, mesh->n, grad_ftle, grad_flow, mesh->bwd_block, s),
+                                         !mesh->symmetric, mesh->n, grad_ftle, grad_flow, mesh->bwd_threads(), s),
                   "adjoint launch");
         check_hip(hipEventRecord(mesh->work_done, s), "hipEventRecord");
         mesh->work_stream = s;
@@ -1900,10 +1909,10 @@ ftle_status ftle_backward_noalloc(ftle_mesh_t mesh, const void* flow, ftle_dtype
         // the tape forward writes every point's tape entry, so nothing is cleared first
         check_hip(launch_forward(mesh->dim, mesh->f64(), mesh->fwd.dev(), mesh->d_x, flow, 0.5 / std::fabs(T),
                                  nullptr, tape, !mesh->symmetric, mesh->n, eig_tau(), mesh->d_hits,
-                                 mesh->fwd_block, s),
+                                 mesh->fwd_threads(), s),
                   "adjoint tape launch");
         check_hip(launch_backward_gather(mesh->dim, mesh->f64(), mesh->adj_tiles().dev(), mesh->d_x, tape,
-                                         !mesh->symmetric, mesh->n, grad_ftle, grad_flow, mesh->bwd_block, s),
+                                         !mesh->symmetric, mesh->n, grad_ftle, grad_flow, mesh->bwd_threads(), s),
                   "adjoint launch");
     });
 }
@@ -2025,6 +2034,7 @@ BatchPlan* get_plan(int n, const ftle_mesh_t* meshes)
 int resident_grid(BatchPlan* p, int block, int per_cu_cap)
 {
     int per_cu = 0;
+    check_hip(allow_lds(batched_kernel_symbol(p->dim, p->f64, block, p->wide), p->lds), "hipFuncSetAttribute");
     check_hip(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batched_kernel_symbol(p->dim, p->f64, block, p->wide),
                                                            block, p->lds),
               "hipOccupancyMaxActiveBlocksPerMultiprocessor");
@@ -2086,6 +2096,7 @@ void build_graph(BatchPlan* p, const BatchCall& call)
     check_hip(hipGraphCreate(&p->graph, 0), "hipGraphCreate");
     hipKernelNodeParams kp{};
     kp.func = const_cast<void*>(batched_kernel_symbol(p->dim, p->f64, p->block, p->wide));
+    check_hip(allow_lds(kp.func, p->lds), "hipFuncSetAttribute");
     kp.gridDim = dim3(p->grid);
     kp.blockDim = dim3(p->block);
     kp.sharedMemBytes = (unsigned)p->lds;
@@ -2234,6 +2245,7 @@ ftle_status ftle_batched(int n, const ftle_mesh_t* meshes, const void* const* fl
                                 call, tau, p->arg_storage.data(), p->args);
             hipKernelNodeParams kp{};
             kp.func = const_cast<void*>(batched_kernel_symbol(p->dim, p->f64, p->block, p->wide));
+    check_hip(allow_lds(kp.func, p->lds), "hipFuncSetAttribute");
             kp.gridDim = dim3(p->grid);
             kp.blockDim = dim3(p->block);
             kp.sharedMemBytes = (unsigned)p->lds;

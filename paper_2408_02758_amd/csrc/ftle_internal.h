@@ -61,7 +61,13 @@ static_assert(sizeof(TileMeta) == 16, "TileMeta is one 16-byte load");
 
 constexpr int kMaxStaged = 1024;       // staged points per tile: 10-bit local indices
 constexpr int kMaxTileWords = 65535;   // stencil words per tile: 16-bit row ends
-constexpr size_t kLdsBudget = 65536;   // LDS bytes one tile may stage (forward or adjoint)
+// LDS bytes one tile may stage (forward or adjoint, with its record at its
+// largest), of a CU's 160 KiB.  3D float64 takes 96 KiB so that its tiles hold
+// 1024 staged points like the others: its adjoint stages 72 bytes a point and
+// one workgroup then fills a CU, but with 64 KiB a tile held 128 points behind
+// a halo three times as large (127 x 113 x 101 points, float64: forward 100 us,
+// with 96 KiB 62; 96^3: 54.5 and 28).
+constexpr size_t lds_budget(int dim, bool f64) { return dim == 3 && f64 ? 98304 : 65536; }
 
 __host__ __device__ inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
@@ -96,7 +102,7 @@ __host__ __device__ inline RecLayout rec_layout(const TileMeta& m)
 //                address reach all three through the instruction's offset
 //   adjoint  2D: one array of round_up(S, 4) slots (x0, x1, w0, w1)
 //                (h0, h1, -, -), 8e
-//            3D: three arrays of bwd3_capacity slots: (x0, x1, x2, h0) and
+//            3D: three arrays of kMaxStaged slots: (x0, x1, x2, h0) and
 //                (h1, h2, w0, w1) (4e each, the second at a fixed offset
 //                from the first), then w2 (e)
 // so that every array and the record copy after them start 16-byte aligned.
@@ -105,13 +111,16 @@ __host__ __device__ inline size_t fwd_points_bytes(int dim, bool f64, int staged
 {
     return dim == 2 ? (size_t)round_up(staged, 4) * 4 * elem_bytes(f64) : (size_t)kMaxStaged * 6 * elem_bytes(f64);
 }
-// Staged points a 3D adjoint tile holds (its arrays have that many slots;
-// float64 tiles are cut smaller to stay in the LDS budget).
-__host__ __device__ constexpr int bwd3_capacity(bool f64) { return f64 ? 512 : kMaxStaged; }
 __host__ __device__ inline size_t bwd_points_bytes(int dim, bool f64, int staged)
 {
     return dim == 2 ? (size_t)round_up(staged, 4) * 8 * elem_bytes(f64)
-                    : (size_t)bwd3_capacity(f64) * 9 * elem_bytes(f64);
+                    : (size_t)kMaxStaged * 9 * elem_bytes(f64);
+}
+
+// Dynamic LDS beyond 64 KiB has to be asked for.
+inline hipError_t allow_lds(const void* kernel, size_t lds)
+{
+    return lds > 65536 ? hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) : hipSuccess;
 }
 
 // One tile set: the tiles of one stencil (the forward stencil, or its

@@ -102,7 +102,7 @@ template <typename V> __device__ inline void lds_st(uint32_t a, const V v) { Lds
 //               reaches all three through the instruction's offset field)
 //   adjoint 2D: (x0, x1, w0, w1) (h0, h1, -, -) at 8e l
 //   adjoint 3D: (x0, x1, x2, h0), (h1, h2, w0, w1) at 4e l + {0, 1} A and
-//               w2 at 2 A + e l, A = 4e bwd3_capacity
+//               w2 at 2 A + e l, A = 4e kMaxStaged
 // so that 16-byte reads are 16-byte aligned and neighbouring points sit in
 // neighbouring banks.  A copy of the tile's record follows.
 // ---------------------------------------------------------------------------
@@ -111,7 +111,7 @@ template <int D, typename T> struct Layout {
     static constexpr uint32_t unit = (D == 2 ? 4 : 2) * e;
     static constexpr uint32_t stride = kMaxStaged * 2 * e;   // 3D forward: array stride
     static constexpr uint32_t bunit = 4 * e;                                   // 3D adjoint: slot of the 4-value arrays
-    static constexpr uint32_t bstride = (uint32_t)bwd3_capacity(e == 8) * bunit;   // and their stride
+    static constexpr uint32_t bstride = kMaxStaged * bunit;   // and their stride
     // LDS address of the record copy after the staged points
     static __device__ uint32_t fwd_rec(uint32_t lds0, int S) { return lds0 + (uint32_t)fwd_points_bytes(D, e == 8, S); }
     static __device__ uint32_t bwd_rec(uint32_t lds0, int S) { return lds0 + (uint32_t)bwd_points_bytes(D, e == 8, S); }
@@ -523,9 +523,9 @@ __device__ __forceinline__ void fwd_compute_tile(const TileMeta m, const T* __re
             const T c11 = j01 * j01 + j11 * j11 + j21 * j21;
             const T c12 = j01 * j02 + j11 * j12 + j21 * j22;
             const T c22 = j02 * j02 + j12 * j12 + j22 * j22;
-            T r, lam;
+            T r;
+            T lam = lam_max3_poly(c00, c01, c02, c11, c12, c22, r);
             if constexpr (sizeof(T) == 4) {
-                lam = lam_max3_poly(c00, c01, c02, c11, c12, c22, r);
                 // Top pair nearly equal: c'(r) amplifies float rounding in r;
                 // redo the tensor and the eigenvalue in double from J.
                 const bool redo = ok && (r + 1.0f < eig_tau);   // (r + 1: no loop-invariant register)
@@ -533,8 +533,6 @@ __device__ __forceinline__ void fwd_compute_tile(const TileMeta m, const T* __re
                     lam = lam_max3_f64_from_J(j00, j01, j02, j10, j11, j12, j20, j21, j22);
                     ++redone;
                 }
-            } else {
-                lam = lam_max3_trig(c00, c01, c02, c11, c12, c22, r);
             }
             f = ok ? log_scaled(lam, inv2T) : quiet_nan<T>();
             if constexpr (TAPE) {
@@ -592,8 +590,10 @@ __device__ __forceinline__ void fwd_tile(const TileMeta m, const uint4* __restri
 
 // float: at most 64 VGPRs (8 waves per SIMD), so that the LDS, not the
 // registers, bounds the workgroups per CU; the tape variant needs the hint.
+// 3D double: at most 128 (4 waves per SIMD, two workgroups of 512 a CU, which
+// the LDS also admits).
 template <int D, typename T, bool OUT, int TAPE, int B, bool WIDE>
-__global__ void __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : 1)))
+__global__ void __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : D == 3 ? 4 : 1)))
 fwd_kernel(const TileMeta* __restrict__ meta, const uint4* __restrict__ rec, int n_tiles, const T* __restrict__ x,
            const T* __restrict__ minv, const T* __restrict__ flow, T inv2T, T* __restrict__ out, T* __restrict__ tape,
            int64_t n, float eig_tau, unsigned long long* hits)
@@ -867,19 +867,22 @@ hipError_t fwd_launch_b(const DevTiles& tiles, const void* x, const void* flow, 
     T* op = static_cast<T*>(out);
     T* tp = static_cast<T*>(tape);
 #define FTLE_FWD_LAUNCH(OUT, TAPE)                                                                              \
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(&fwd_kernel<D, T, OUT, TAPE, B, WIDE>), lds);  \
+    if (e != hipSuccess) return e;                                                                              \
     hipLaunchKernelGGL((fwd_kernel<D, T, OUT, TAPE, B, WIDE>), grid, blk, lds, stream, tiles.meta, tiles.rec,   \
                        tiles.n_tiles, xp, static_cast<const T*>(tiles.minv), fp, (T)inv2T, op, tp, n,             \
                        (float)eig_tau, hits)
-    if (!tape)
+    if (!tape) {
         FTLE_FWD_LAUNCH(true, 0);
-    else if (out && tape_sigma)
+    } else if (out && tape_sigma) {
         FTLE_FWD_LAUNCH(true, 2);
-    else if (out)
+    } else if (out) {
         FTLE_FWD_LAUNCH(true, 1);
-    else if (tape_sigma)
+    } else if (tape_sigma) {
         FTLE_FWD_LAUNCH(false, 2);
-    else
+    } else {
         FTLE_FWD_LAUNCH(false, 1);
+    }
 #undef FTLE_FWD_LAUNCH
     return hipGetLastError();
 }
@@ -889,15 +892,15 @@ hipError_t bwd_launch_b(const DevTiles& tiles, const void* x, const void* tape, 
                         const void* g, void* grad, hipStream_t stream)
 {
     const size_t lds = bwd_lds<D, T>(tiles);
-    if (tape_sigma)
-        hipLaunchKernelGGL((bwd_kernel<D, T, B, WIDE, true>), dim3(tiles.n_tiles), dim3(B), lds, stream, tiles.meta,
-                           tiles.rec, tiles.n_tiles, static_cast<const T*>(x), static_cast<const T*>(tape), n,
-                           static_cast<const T*>(g), static_cast<T*>(grad));
-    else
-        hipLaunchKernelGGL((bwd_kernel<D, T, B, WIDE, false>), dim3(tiles.n_tiles), dim3(B), lds, stream, tiles.meta,
-                           tiles.rec, tiles.n_tiles, static_cast<const T*>(x), static_cast<const T*>(tape), n,
-                           static_cast<const T*>(g), static_cast<T*>(grad));
-    return hipGetLastError();
+    const auto launch = [&](auto kernel) {
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(tiles.n_tiles), dim3(B), lds, stream, tiles.meta, tiles.rec, tiles.n_tiles,
+                           static_cast<const T*>(x), static_cast<const T*>(tape), n, static_cast<const T*>(g),
+                           static_cast<T*>(grad));
+        return hipGetLastError();
+    };
+    return tape_sigma ? launch(&bwd_kernel<D, T, B, WIDE, true>) : launch(&bwd_kernel<D, T, B, WIDE, false>);
 }
 
 // 32-bit byte offsets reach every array of an n-point mesh when the largest
@@ -1147,6 +1150,8 @@ hipError_t launch_batched(int dim, bool f64, bool wide, const BatchItem* items, 
 {
     const void* k = batched_kernel_symbol(dim, f64, block, wide);
     if (!k) return hipErrorInvalidValue;
+    const hipError_t e = allow_lds(k, lds);
+    if (e != hipSuccess) return e;
     BatchArgs storage;
     void* args[6];
     batched_kernel_args(items, n_items, tiles_per_pop, queue, call, eig_tau, &storage, args);

@@ -1143,11 +1143,8 @@ hipError_t mb_tile_record(const int64_t* row_ptr, const int32_t* col, const uint
 {
     if (n_tiles == 0) return hipSuccess;
     const size_t lds = 4 * (size_t)max_words;
-    if (sizeof(TileScratch) + lds > 65536) {   // more than the default limit (rows of many entries)
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_record),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(&tile_record), sizeof(TileScratch) + lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(tile_record, dim3((unsigned)n_tiles), dim3(kTileThreads), lds, s, row_ptr, col, perm, ranges,
                        stage_off, counts, stage);
     return hipGetLastError();

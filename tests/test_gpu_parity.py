@@ -257,6 +257,35 @@ def test_adjoint_vs_oracle(dim, dtype, stencil):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n,tile_log2", [(9, 5), (13, 7), (17, 8), (20, 9), (24, 10), (24, 11)])
+def test_3d_tile_sizes_and_threads(dtype, n, tile_log2):
+    """Every launch width a tile size leads to (128 threads for tiles of at most
+    128 points, 256, 512, and tiles of more points than threads), with tiles up
+    to 1024 staged points (over 64 KiB of LDS in the float64 adjoint): forward
+    at the tolerances above, adjoint within 1e-10 (float64) or 2e-4 (float32)
+    of the largest gradient entry.  The top eigenvector carries about ten
+    roundings over the gap: points with a gap below 1e-2 (float32) or 1e-4
+    (float64), where that alone nears the tolerance, get no weight."""
+    w = configs.abc3d(n, 2.0, dtype)
+    mesh = F.Mesh(w.coords, w.cells, dtype, tile_log2=tile_log2)
+    x, phi = w.coords.astype(np.float64), w.flow_numpy().astype(np.float64)
+    st = oracle.ring1(3, w.n, w.cells)
+    ref, gap = oracle.ftle(3, x, phi, st, w.T, diagnostics=True)[:2]
+    flow = w.flow.to(DEV).contiguous()
+    got = mesh.forward(flow, w.T).cpu().numpy().astype(np.float64)
+    tag = f"abc {n}^3 {dtype} tile {tile_log2}"
+    if dtype == "f64":
+        check_f64(tag, got, ref, gap, w.T, 3)
+    else:
+        check_f32(tag, got, ref, gap, w.T)
+    g = np.random.default_rng(n).standard_normal(w.n).astype(w.coords.dtype)
+    g[~(gap >= (1e-4 if dtype == "f64" else 1e-2))] = 0.0
+    gref = oracle.ftle_grad(3, x, phi, st, w.T, g.astype(np.float64))
+    grad = mesh.backward(flow, w.T, torch.as_tensor(g, device=DEV)).cpu().numpy()
+    assert np.abs(grad - gref).max() <= (1e-10 if dtype == "f64" else 2e-4) * np.abs(gref).max()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("relabel", [True, False])
 def test_3d_records_worst_case_and_empty_rows(dtype, relabel):
     """Compressed records at their worst and at edges: a 3D grid plus a
