@@ -17,9 +17,18 @@ from ._lib import FTLEError, check
 _DT = {"f32": (_lib.F32, np.float32, torch.float32), "f64": (_lib.F64, np.float64, torch.float64)}
 
 
+# The current stream's handle without building a torch.cuda.Stream object: 0.06
+# us instead of 2.5, of the 8.5 us a small forward call took on the host.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_handle(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 class Mesh:
@@ -120,9 +129,9 @@ class Mesh:
             flags |= _lib.NO_REORDER
         h = ctypes.c_void_p()
         ncells = cells.shape[0]
-        check(_lib.load().ftle_create_mesh_device(dim, coords.shape[0], ctypes.c_void_p(coords.data_ptr()),
+        check(_lib.load().ftle_create_mesh_device(dim, coords.shape[0], coords.data_ptr(),
                                                   _DT[dtype][0], ncells,
-                                                  ctypes.c_void_p(cells.data_ptr()) if ncells else None, flags,
+                                                  cells.data_ptr() if ncells else None, flags,
                                                   _stream_handle(stream), ctypes.byref(h)))
         m = cls.__new__(cls)
         m._init(h, dim, coords.shape[0], dtype, False)
@@ -152,8 +161,8 @@ class Mesh:
             flags |= _lib.NO_REORDER
         h = ctypes.c_void_p()
         check(_lib.load().ftle_create_mesh_device_from_csr(
-            dim, n, ctypes.c_void_p(coords.data_ptr()), _DT[dtype][0], ctypes.c_void_p(row_ptr.data_ptr()),
-            ctypes.c_void_p(col.data_ptr()) if col.numel() else None, flags, _stream_handle(stream),
+            dim, n, coords.data_ptr(), _DT[dtype][0], row_ptr.data_ptr(),
+            col.data_ptr() if col.numel() else None, flags, _stream_handle(stream),
             ctypes.byref(h)))
         m = cls.__new__(cls)
         m._init(h, dim, n, dtype, False)
@@ -287,7 +296,7 @@ class Mesh:
             raise TypeError(f"{name} must be a CUDA (HIP) tensor")
         if t.dtype != self.torch_dtype:
             raise TypeError(f"{name} must have dtype {self.torch_dtype}")
-        if tuple(t.shape) != tuple(shape):
+        if t.shape != shape:
             raise ValueError(f"{name} must have shape {shape}, got {tuple(t.shape)}")
         if not t.is_contiguous():
             raise ValueError(f"{name} must be contiguous")
@@ -296,9 +305,10 @@ class Mesh:
         self._check_flow(flow)
         if out is None:
             out = torch.empty(self.n, dtype=self.torch_dtype, device=flow.device)
-        self._check_flow(out, "out", (self.n,))
-        check(_lib.load().ftle_forward(self._h, ctypes.c_void_p(flow.data_ptr()), self._code, float(T),
-                                       ctypes.c_void_p(out.data_ptr()), _stream_handle(stream)))
+        else:
+            self._check_flow(out, "out", (self.n,))
+        check(_lib.load().ftle_forward(self._h, flow.data_ptr(), self._code, float(T),
+                                       out.data_ptr(), _stream_handle(stream)))
         return out
 
     def encode_flow_f16(self, flow: torch.Tensor, out: torch.Tensor | None = None, stream=None) -> torch.Tensor:
@@ -309,8 +319,8 @@ class Mesh:
             out = torch.empty(self.n, 2, dtype=torch.float16, device=flow.device)
         if not (out.is_cuda and out.dtype == torch.float16 and out.is_contiguous() and tuple(out.shape) == (self.n, 2)):
             raise ValueError(f"out must be a contiguous float16 device tensor of shape ({self.n}, 2)")
-        check(_lib.load().ftle_encode_flow_f16(self._h, ctypes.c_void_p(flow.data_ptr()),
-                                               ctypes.c_void_p(out.data_ptr()), _stream_handle(stream)))
+        check(_lib.load().ftle_encode_flow_f16(self._h, flow.data_ptr(),
+                                               out.data_ptr(), _stream_handle(stream)))
         return out
 
     def forward_f16(self, delta: torch.Tensor, T: float, out: torch.Tensor | None = None, stream=None):
@@ -322,20 +332,22 @@ class Mesh:
         if out is None:
             out = torch.empty(self.n, dtype=torch.float32, device=delta.device)
         self._check_flow(out, "out", (self.n,))
-        check(_lib.load().ftle_forward_f16(self._h, ctypes.c_void_p(delta.data_ptr()), float(T),
-                                           ctypes.c_void_p(out.data_ptr()), _stream_handle(stream)))
+        check(_lib.load().ftle_forward_f16(self._h, delta.data_ptr(), float(T),
+                                           out.data_ptr(), _stream_handle(stream)))
         return out
 
     def forward_tape(self, flow: torch.Tensor, T: float, out=None, tape=None, stream=None):
         self._check_flow(flow)
         if out is None:
             out = torch.empty(self.n, dtype=self.torch_dtype, device=flow.device)
+        else:
+            self._check_flow(out, "out", (self.n,))
         if tape is None:
             tape = torch.empty(self.n * (2 * self.dim + 1), dtype=self.torch_dtype, device=flow.device)
-        self._check_flow(out, "out", (self.n,))
-        self._check_flow(tape, "tape", (self.n * (2 * self.dim + 1),))
-        check(_lib.load().ftle_forward_tape(self._h, ctypes.c_void_p(flow.data_ptr()), self._code, float(T),
-                                            ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(tape.data_ptr()),
+        else:
+            self._check_flow(tape, "tape", (self.n * (2 * self.dim + 1),))
+        check(_lib.load().ftle_forward_tape(self._h, flow.data_ptr(), self._code, float(T),
+                                            out.data_ptr(), tape.data_ptr(),
                                             _stream_handle(stream)))
         return out, tape
 
@@ -344,10 +356,11 @@ class Mesh:
         self._check_flow(grad_ftle, "grad_ftle", (self.n,))
         if grad_flow is None:
             grad_flow = torch.empty(self.n, self.dim, dtype=self.torch_dtype, device=tape.device)
-        self._check_flow(grad_flow, "grad_flow")
-        check(_lib.load().ftle_backward_tape(self._h, ctypes.c_void_p(tape.data_ptr()), self._code,
-                                             ctypes.c_void_p(grad_ftle.data_ptr()),
-                                             ctypes.c_void_p(grad_flow.data_ptr()), _stream_handle(stream)))
+        else:
+            self._check_flow(grad_flow, "grad_flow")
+        check(_lib.load().ftle_backward_tape(self._h, tape.data_ptr(), self._code,
+                                             grad_ftle.data_ptr(),
+                                             grad_flow.data_ptr(), _stream_handle(stream)))
         return grad_flow
 
     def backward(self, flow: torch.Tensor, T: float, grad_ftle: torch.Tensor, grad_flow=None, stream=None):
@@ -356,9 +369,9 @@ class Mesh:
         if grad_flow is None:
             grad_flow = torch.empty(self.n, self.dim, dtype=self.torch_dtype, device=flow.device)
         self._check_flow(grad_flow, "grad_flow")
-        check(_lib.load().ftle_backward(self._h, ctypes.c_void_p(flow.data_ptr()), self._code, float(T),
-                                        ctypes.c_void_p(grad_ftle.data_ptr()),
-                                        ctypes.c_void_p(grad_flow.data_ptr()), _stream_handle(stream)))
+        check(_lib.load().ftle_backward(self._h, flow.data_ptr(), self._code, float(T),
+                                        grad_ftle.data_ptr(),
+                                        grad_flow.data_ptr(), _stream_handle(stream)))
         return grad_flow
 
     def backward_noalloc(self, flow: torch.Tensor, T: float, grad_ftle: torch.Tensor, grad_flow: torch.Tensor,
@@ -369,9 +382,9 @@ class Mesh:
         self._check_flow(flow)
         self._check_flow(grad_ftle, "grad_ftle", (self.n,))
         self._check_flow(grad_flow, "grad_flow")
-        check(_lib.load().ftle_backward_noalloc(self._h, ctypes.c_void_p(flow.data_ptr()), self._code, float(T),
-                                                ctypes.c_void_p(grad_ftle.data_ptr()),
-                                                ctypes.c_void_p(grad_flow.data_ptr()), _stream_handle(stream)))
+        check(_lib.load().ftle_backward_noalloc(self._h, flow.data_ptr(), self._code, float(T),
+                                                grad_ftle.data_ptr(),
+                                                grad_flow.data_ptr(), _stream_handle(stream)))
         return grad_flow
 
     def fp64_hits(self, reset: bool = False) -> int:
@@ -490,7 +503,7 @@ def advect_rk4(flow: str, x0: torch.Tensor, t0, T, dt: float, params=None, out: 
         if isinstance(v, torch.Tensor):
             if not (v.is_cuda and v.dtype == torch.float64 and v.is_contiguous() and v.shape == (n,)):
                 raise ValueError(f"{name} must be a contiguous float64 device tensor of {n} values")
-            return ctypes.c_void_p(v.data_ptr()), 0.0
+            return v.data_ptr(), 0.0
         return None, float(v)
 
     t0p, t0s = per_point(t0, "t0")
@@ -499,8 +512,8 @@ def advect_rk4(flow: str, x0: torch.Tensor, t0, T, dt: float, params=None, out: 
         out = torch.empty_like(x0)
     _check_out(out, x0.shape, x0.dtype, not_alias=x0)
     prm = None if params is None else (ctypes.c_double * 3)(*[float(v) for v in params])
-    check(_lib.load().ftle_advect_rk4(kind, prm, n, ctypes.c_void_p(x0.data_ptr()), code, t0p, Tp, t0s, Ts,
-                                      float(dt), ctypes.c_void_p(out.data_ptr()), _stream_handle(stream)))
+    check(_lib.load().ftle_advect_rk4(kind, prm, n, x0.data_ptr(), code, t0p, Tp, t0s, Ts,
+                                      float(dt), out.data_ptr(), _stream_handle(stream)))
     return out
 
 
@@ -527,7 +540,7 @@ def advect_rk4_grid(velocity: torch.Tensor, origin, spacing, t_first: float, t_s
         if isinstance(v, torch.Tensor):
             if not (v.is_cuda and v.dtype == torch.float64 and v.is_contiguous() and v.shape == (n,)):
                 raise ValueError(f"{name} must be a contiguous float64 device tensor of {n} values")
-            return ctypes.c_void_p(v.data_ptr()), 0.0
+            return v.data_ptr(), 0.0
         return None, float(v)
 
     t0p, t0s = per_point(t0, "t0")
@@ -541,9 +554,9 @@ def advect_rk4_grid(velocity: torch.Tensor, origin, spacing, t_first: float, t_s
     org = (ctypes.c_double * dim)(*[float(v) for v in origin])
     spc = (ctypes.c_double * dim)(*[float(v) for v in spacing])
     check(_lib.load().ftle_advect_rk4_grid(
-        dim, shape, org, spc, velocity.shape[0], float(t_first), float(t_step), ctypes.c_void_p(velocity.data_ptr()),
-        1 if velocity.dtype == torch.float64 else 0, n, ctypes.c_void_p(x0.data_ptr()),
-        1 if x0.dtype == torch.float64 else 0, t0p, Tp, t0s, Ts, float(dt), ctypes.c_void_p(out.data_ptr()),
+        dim, shape, org, spc, velocity.shape[0], float(t_first), float(t_step), velocity.data_ptr(),
+        1 if velocity.dtype == torch.float64 else 0, n, x0.data_ptr(),
+        1 if x0.dtype == torch.float64 else 0, t0p, Tp, t0s, Ts, float(dt), out.data_ptr(),
         _stream_handle(stream)))
     return out
 
@@ -576,14 +589,14 @@ def ring1_csr(dim: int, n_points: int, cells: torch.Tensor, stream=None, workspa
         raise ValueError("col must be a contiguous int32 device tensor")
     nnz = ctypes.c_int64(0)
     L = _lib.load()
-    args = [dim, int(n_points), n_cells, ctypes.c_void_p(cells.data_ptr()), ctypes.c_void_p(row_ptr.data_ptr()),
-            ctypes.c_void_p(col.data_ptr()), col.numel(), ctypes.byref(nnz)]
+    args = [dim, int(n_points), n_cells, cells.data_ptr(), row_ptr.data_ptr(),
+            col.data_ptr(), col.numel(), ctypes.byref(nnz)]
     if workspace is None:
         check(L.ftle_ring1_csr(*args, _stream_handle(stream)))
     else:
         if not (workspace.is_cuda and workspace.is_contiguous()):
             raise ValueError("workspace must be a contiguous device tensor")
-        check(L.ftle_ring1_csr_ws(*args, ctypes.c_void_p(workspace.data_ptr()),
+        check(L.ftle_ring1_csr_ws(*args, workspace.data_ptr(),
                                   workspace.numel() * workspace.element_size(), _stream_handle(stream)))
     return row_ptr, col[:nnz.value]
 
@@ -606,9 +619,9 @@ def axis_ell(coords: torch.Tensor, row_ptr: torch.Tensor, col: torch.Tensor, str
         raise ValueError("col must be a contiguous int32 device tensor")
     ell = torch.empty(n, 2 * dim, dtype=torch.int32, device=coords.device)
     code = _lib.F64 if coords.dtype == torch.float64 else _lib.F32
-    check(_lib.load().ftle_axis_ell(dim, n, ctypes.c_void_p(coords.data_ptr()), code,
-                                    ctypes.c_void_p(row_ptr.data_ptr()), ctypes.c_void_p(col.data_ptr()),
-                                    ctypes.c_void_p(ell.data_ptr()), _stream_handle(stream)))
+    check(_lib.load().ftle_axis_ell(dim, n, coords.data_ptr(), code,
+                                    row_ptr.data_ptr(), col.data_ptr(),
+                                    ell.data_ptr(), _stream_handle(stream)))
     return ell
 
 
@@ -628,9 +641,9 @@ def forward_ell(coords: torch.Tensor, ell: torch.Tensor, flow: torch.Tensor, T: 
         out = torch.empty(n, dtype=coords.dtype, device=coords.device)
     _check_out(out, (n,), coords.dtype)
     code = _lib.F64 if coords.dtype == torch.float64 else _lib.F32
-    check(_lib.load().ftle_forward_ell(dim, n, ctypes.c_void_p(coords.data_ptr()), code,
-                                       ctypes.c_void_p(ell.data_ptr()), ctypes.c_void_p(flow.data_ptr()), float(T),
-                                       ctypes.c_void_p(out.data_ptr()),
+    check(_lib.load().ftle_forward_ell(dim, n, coords.data_ptr(), code,
+                                       ell.data_ptr(), flow.data_ptr(), float(T),
+                                       out.data_ptr(),
                                        _lib.ELL_STAGED if staged else _lib.ELL_DIRECT, _stream_handle(stream)))
     return out
 
