@@ -279,9 +279,11 @@ void ftle_destroy_mesh(ftle_mesh_t mesh);
  * The device mesh builds (ftle_create_mesh_device*) and ftle_ring1_csr keep
  * their temporary device memory per device between calls, grown when a call
  * needs more, so that repeated calls do not allocate and free it each time (a
- * few hundred bytes per point: 1.5 GB for a 4.1 M-point tetrahedral mesh).
- * ftle_cached_memory_bytes reports how much is held (all devices);
- * ftle_release_cached_memory frees what no build is using.
+ * few hundred bytes per point: 1.5 GB for a 4.1 M-point tetrahedral mesh).  The
+ * memory of destroyed meshes is likewise kept for the next ones, up to 1 GiB
+ * per device, and freed before an allocation of the library would fail.
+ * ftle_cached_memory_bytes reports how much is held and not in use by a mesh
+ * (all devices); ftle_release_cached_memory frees what no build is using.
  * Errors: INVALID_ARG (bytes NULL), DEVICE.
  */
 ftle_status ftle_cached_memory_bytes(int64_t* bytes);

@@ -457,3 +457,42 @@ def test_build_scratch_is_kept_and_released():
             ma, ra = _raw_tiles(a, adjoint)
             mm, rm = _raw_tiles(m, adjoint)
             assert np.array_equal(ma, mm) and np.array_equal(ra, rm)
+
+
+def test_mesh_memory_is_reused_and_bounded():
+    """A destroyed mesh's memory serves the next one: repeated builds of changing
+    sizes, two at a time on their own threads and streams, keep giving the host
+    build's records; what is kept stays within its bound and is given back."""
+    import threading
+    F.release_cached_memory()
+    geo = [meshes.kuhn_tet_grid(n) for n in (9, 14, 11)] + [meshes.jittered_tri_grid(60, 40, seed=2)]
+    want = [_raw_tiles(F.Mesh(x, cells, "f32")) for x, cells in geo]
+    wrong = []
+
+    def work(first):
+        s = torch.cuda.Stream()
+        for k in range(12):
+            x, cells = geo[(first + k) % len(geo)]
+            with torch.cuda.stream(s):
+                m = _device_mesh(x, cells, "f32")
+                phi = torch.as_tensor(_flow(x, k), dtype=torch.float32, device=DEV)
+                f = m.forward(phi, 1.5)
+                got = _raw_tiles(m)
+                fine = torch.isfinite(f).all().item()
+            if not (fine and all(np.array_equal(a, b) for a, b in zip(got, want[(first + k) % len(geo)]))):
+                wrong.append((first, k))
+            m.close()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in (0, 2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    held = F.cached_memory_bytes()
+    assert 0 < held < 2 ** 30 + 2 ** 28
+    again = [_device_mesh(*g, "f32") for g in geo]
+    assert F.cached_memory_bytes() <= held
+    del again
+    F.release_cached_memory()
+    assert F.cached_memory_bytes() == 0
