@@ -1,7 +1,7 @@
-// Device helpers shared by the FTLE kernels (ftle_kernels.hip, ftle_ell.hip):
-// the XCD-aware workgroup order, precision-explicit arithmetic, the rank
-// threshold of the least-squares solve, and the closed-form largest
-// eigenvalue of a symmetric 3x3 tensor with its float64 recompute.  Device
+// Device helpers shared by the kernels: the XCD-aware workgroup order,
+// precision-explicit arithmetic, the rank threshold of the least-squares solve,
+// the closed-form largest eigenvalue of a symmetric 3x3 tensor with its float64
+// recompute, and a sorting network.  Device
 // code only; every function has internal linkage, so each translation unit
 // has its own copy.
 #pragma once
@@ -152,6 +152,34 @@ __device__ __noinline__ float lam_max3_f64_from_J(float j00, float j01, float j0
                                       e00 * e02 + e10 * e12 + e20 * e22, e01 * e01 + e11 * e11 + e21 * e21,
                                       e01 * e02 + e11 * e12 + e21 * e22, e02 * e02 + e12 * e12 + e22 * e22, rd);
     return (float)lamd;
+}
+
+// Batcher's odd-even merge sort of N values in registers, ascending.
+template <int LO, int N, int R, int M>
+__device__ inline void odd_even_merge(uint32_t (&v)[M])
+{
+    auto order = [&](int i, int j) {
+        const uint32_t a = min(v[i], v[j]), b = max(v[i], v[j]);
+        v[i] = a;
+        v[j] = b;
+    };
+    if constexpr (2 * R < N) {
+        odd_even_merge<LO, N, 2 * R>(v);
+        odd_even_merge<LO + R, N, 2 * R>(v);
+#pragma unroll
+        for (int i = LO + R; i + R < LO + N; i += 2 * R) order(i, i + R);
+    } else {
+        order(LO, LO + R);
+    }
+}
+template <int LO, int N, int M>
+__device__ inline void odd_even_sort(uint32_t (&v)[M])
+{
+    if constexpr (N > 1) {
+        odd_even_sort<LO, N / 2>(v);
+        odd_even_sort<LO + N / 2, N / 2>(v);
+        odd_even_merge<LO, N, 1>(v);
+    }
 }
 
 }  // namespace

@@ -465,34 +465,6 @@ __device__ inline void sort_keys(uint64_t* s, int m, int t)
     __syncthreads();
 }
 
-// Batcher's odd-even merge sort of N values in registers, ascending.
-template <int LO, int N, int R, int M>
-__device__ inline void odd_even_merge(uint32_t (&v)[M])
-{
-    auto order = [&](int i, int j) {
-        const uint32_t a = min(v[i], v[j]), b = max(v[i], v[j]);
-        v[i] = a;
-        v[j] = b;
-    };
-    if constexpr (2 * R < N) {
-        odd_even_merge<LO, N, 2 * R>(v);
-        odd_even_merge<LO + R, N, 2 * R>(v);
-#pragma unroll
-        for (int i = LO + R; i + R < LO + N; i += 2 * R) order(i, i + R);
-    } else {
-        order(LO, LO + R);
-    }
-}
-template <int LO, int N, int M>
-__device__ inline void odd_even_sort(uint32_t (&v)[M])
-{
-    if constexpr (N > 1) {
-        odd_even_sort<LO, N / 2>(v);
-        odd_even_sort<LO + N / 2, N / 2>(v);
-        odd_even_merge<LO, N, 1>(v);
-    }
-}
-
 // LDS of tile_record besides its row words.
 struct TileScratch {
     int32_t keys[kHashSlots];         // halo hash set (Morton positions)

@@ -17,14 +17,11 @@
 //      add_partials: 2048-element tiles, the tiles' sums scanned by one
 //      workgroup, then added back), and
 //   3. a second pass appends each cell's index to its points' packed lists;
-//   4. rows: one lane per point walks its incident cells and inserts their
-//      other points into a short sorted list of distinct indices in LDS, each
-//      one's place found by binary search (a lane's list is interleaved with
-//      its workgroup's, so that a list step is one conflict-free LDS access),
-//      then stores its count and the list (a fixed kRowCap slots per point in
-//      the workspace); the counts are scanned into the row pointers, and a
-//      copy moves the lists into place.
-//      A point with more than kRowCap distinct neighbours is handed to a
+//   4. rows: one lane per point walks its incident cells and collects their
+//      points in a sorted list in registers, then stores its count and the list
+//      (a fixed kRowCap slots per point in the workspace); the counts are
+//      scanned into the row pointers, and a copy moves the lists into place.
+//      A point with more than kRowCap - 2 distinct neighbours is handed to a
 //      workgroup of its own (long_rows: its candidates sorted by a bitonic
 //      network in LDS, duplicates dropped by a flag scan), once to count and
 //      once to write.
@@ -41,7 +38,7 @@ namespace {
 
 constexpr int kScanThreads = 256, kScanItems = 8, kScanTile = kScanThreads * kScanItems;
 constexpr int kRowThreads = 128;   // lanes per workgroup of the row passes
-constexpr int kRowCap = 32;        // distinct neighbours a lane keeps in LDS
+constexpr int kRowCap = 32;        // list entries a lane keeps in registers (the point and one free among them)
 constexpr int kLongCap = 4096;     // candidates (with repeats) of a long row
 constexpr uint32_t kIncCap2 = 16, kIncCap3 = 32;   // fixed incidence list length (triangles, tetrahedra)
 
@@ -68,6 +65,13 @@ __device__ inline void load_cell(const int32_t* __restrict__ cells, int64_t c, i
 // costs one global atomic instead of one per occurrence: cells come in mesh
 // order, and neighbouring cells share most of their points.  A point that
 // finds no slot within kProbes probes goes to global memory directly.
+// The pass waits for those atomics' round trips (83 % of its wave cycles), so
+// the used slots are listed as they fill and a lane has one or two atomics one
+// after the other instead of one per slot of the table: 127 x 113 x 101 points
+// 310 -> 185 us, 1023 x 769 triangle mesh 78 -> 33.  512 threads of two cells
+// and 8192 slots: 1024 threads of one cell take 152 us there but lose on cells
+// in random order (every point distinct; 70^3: 620 us as before, 707 with
+// 1024, 560 with 512).
 //   kCount:  cnt[v] += occurrences of v (a cell with an index outside [0, n)
 //            sets bit 1 of *err and adds nothing);
 //   kPacked: each occurrence of v gets a position from cur[v] (the workgroup
@@ -76,10 +80,10 @@ __device__ inline void load_cell(const int32_t* __restrict__ cells, int64_t c, i
 //   kFixed:  as kCount, and each occurrence of v also gets list position
 //            k = the count before it, inc[v cap + k] = its cell while k < cap
 //            (beyond it, bit 4 of *err and no store).
-constexpr int kAggThreads = 256, kAggCells = 4, kAggSlots = 4096, kProbes = 32;
+constexpr int kAggThreads = 512, kAggCells = 2, kAggSlots = 8192, kProbes = 16;
 enum IncMode { kCount, kPacked, kFixed };
 
-__device__ inline uint32_t agg_hash(int32_t v) { return ((uint32_t)v * 2654435761u) >> 20; }   // 12 bits
+__device__ inline uint32_t agg_hash(int32_t v) { return ((uint32_t)v * 2654435761u) >> 19; }   // 13 bits
 
 template <int K, int MODE>
 __global__ void __launch_bounds__(kAggThreads) incidence_pass(const int32_t* __restrict__ cells, int64_t n_cells,
@@ -88,14 +92,17 @@ __global__ void __launch_bounds__(kAggThreads) incidence_pass(const int32_t* __r
                                                               uint32_t cap)
 {
     constexpr bool FILL = MODE != kCount;
-    static_assert(kAggSlots == 1 << 12, "agg_hash gives 12 bits");
+    static_assert(kAggSlots == 1 << 13, "agg_hash gives 13 bits");
     __shared__ int32_t key[kAggSlots];
     __shared__ uint32_t num[kAggSlots];
+    __shared__ uint16_t used[kAggThreads * kAggCells * K];   // the slots in use
+    __shared__ int n_used;
     const int t = (int)threadIdx.x;
     for (int i = t; i < kAggSlots; i += kAggThreads) {
         key[i] = -1;
         num[i] = 0;
     }
+    if (t == 0) n_used = 0;
     __syncthreads();
     // each XCD takes a contiguous stretch of cells (its L2 then holds their points' counters)
     const int64_t c0 = (int64_t)xcd_tile((int)blockIdx.x, (int)gridDim.x) * (kAggThreads * kAggCells);
@@ -120,6 +127,7 @@ __global__ void __launch_bounds__(kAggThreads) incidence_pass(const int32_t* __r
             int s = -1;
             for (int p = 0; p < kProbes; ++p, h = (h + 1) & (kAggSlots - 1)) {
                 const int32_t k = atomicCAS(&key[h], -1, v[a]);
+                if (k == -1) used[atomicAdd(&n_used, 1)] = (uint16_t)h;
                 if (k == -1 || k == v[a]) {
                     s = (int)h;
                     break;
@@ -142,13 +150,14 @@ __global__ void __launch_bounds__(kAggThreads) incidence_pass(const int32_t* __r
         }
     }
     __syncthreads();
-    for (int i = t; i < kAggSlots; i += kAggThreads) {
-        const int32_t k = key[i];
-        if (k < 0) continue;
+    // (over the used slots, not the table: a global atomic's round trip is
+    // several microseconds here, and a lane has three of them, not sixteen)
+    for (int j = t; j < n_used; j += kAggThreads) {
+        const int i = used[j];
         if (FILL)
-            num[i] = atomicAdd(&cnt[k], num[i]);   // the block's first position
+            num[i] = atomicAdd(&cnt[key[i]], num[i]);   // the block's first position
         else
-            atomicAdd(&cnt[k], num[i]);
+            atomicAdd(&cnt[key[i]], num[i]);
     }
     if constexpr (MODE == kPacked) {
         __syncthreads();
@@ -258,11 +267,10 @@ hipError_t exclusive_scan(const uint32_t* in, int64_t m, Out* out, Out* partial,
 }
 
 // ---------------------------------------------------------------------------
-// 4. rows.  Lane r (point r) keeps its distinct neighbours, ascending, in
-// lst[k * kRowThreads + lane], k < kRowCap, then sets deg[r] to their count
-// and stores them at store[k * n + r] (entry-major, so that each store
-// instruction writes consecutive points).  A point with more is appended to
-// longs (deg[r] = 0 until long_rows counts it).
+// 4. rows.  Lane r (point r) collects its distinct neighbours, at most kRowCap - 2,
+// sets deg[r] to their count and stores them, ascending, at store[k * n + r]
+// (entry-major, so that each store instruction writes consecutive points).  A
+// point with more is appended to longs (deg[r] = 0 until long_rows counts it).
 // ---------------------------------------------------------------------------
 // Point r's incidence list: inc[p0, p1).  *capp = 0: packed lists at the
 // offsets off[r], off[r + 1]; otherwise fixed lists of *capp entries, off[r]
@@ -279,68 +287,140 @@ __device__ inline IncRange inc_range(const uint32_t* __restrict__ off, uint32_t 
     return IncRange{off[r], off[r + 1]};
 }
 
-template <int K>
-__global__ void __launch_bounds__(kRowThreads) ring_rows(const int32_t* __restrict__ cells,
-                                                         const int32_t* __restrict__ inc,
-                                                         const uint32_t* __restrict__ off,
-                                                         const uint32_t* __restrict__ capp, int64_t n,
-                                                         uint32_t* __restrict__ deg, int32_t* __restrict__ store,
-                                                         uint32_t* __restrict__ longs, uint32_t* __restrict__ n_long)
+// The list lives in registers, the point itself among its entries (so that it
+// counts as found): every candidate is compared with all N entries and, where
+// some lane's is new, inserted by one v_med3 per entry, without a branch or a
+// memory access per lane.  127 x 113 x 101 points: 304 -> 155 us; 1023 x 769
+// triangle mesh 44 -> 27.  (A sorted list in LDS, searched by bisection and
+// moved up entry by entry, waited on LDS for 61 % of its cycles and executed
+// 4400 vector instructions a wave at 24 cells a point; now 2900.)
+//
+// N = 16 serves waves whose points have at most 14 neighbours by the count of
+// their incident cells (a closed fan of m triangles has m other points, a
+// closed ball of m tetrahedra m / 2 + 2); a list that fills up (a point on the
+// boundary has more) is collected again with N = 32.
+constexpr uint32_t kNone = 0xffffffffu;
+
+// The points of kBatch cells into the list.
+template <int K, int N, int BATCH>
+__device__ inline void collect_cells(const int32_t* __restrict__ cells, const int32_t (&c)[BATCH], uint32_t (&s)[N])
 {
-    __shared__ int32_t lst[kRowCap * kRowThreads];
-    const int t = (int)threadIdx.x;
-    const int64_t r = (int64_t)xcd_tile((int)blockIdx.x, (int)gridDim.x) * kRowThreads + t;   // XCD-contiguous rows
-    if (r >= n) return;
-    int32_t* my = lst + t;   // entry k at my[k * kRowThreads]
-    int cnt = 0;
-    bool over = false;
-    const IncRange ir = inc_range(off, *capp, r);
-    const uint32_t p0 = ir.p0, p1 = ir.p1;
-    // incident cells kChunk at a time: their loads are issued together, then
-    // their points are inserted (a cell past the end repeats the last one,
-    // whose points are then found already listed)
-    constexpr int kChunk = 4;
-    for (uint32_t p = p0; p < p1 && !over; p += kChunk) {
-        int32_t v[kChunk][K];
-        int32_t c[kChunk];
+    int32_t v[BATCH][K];
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) c[q] = inc[min(p + q, p1 - 1)];
+    for (int q = 0; q < BATCH; ++q) load_cell<K>(cells, c[q], v[q]);
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) load_cell<K>(cells, c[q], v[q]);
+    for (int q = 0; q < BATCH; ++q)
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q)
+        for (int a = 0; a < K; ++a) {
+            uint32_t u = (uint32_t)v[q][a];
+            bool f[4] = {false, false, false, false};   // four short chains
 #pragma unroll
-            for (int a = 0; a < K; ++a) {
-                const int32_t u = v[q][a];
-                if (u == (int32_t)r || over) continue;
-                // insertion point k: the number of listed entries below u, by
-                // binary search (at most 6 steps for 32 entries)
-                int k = 0, hi = cnt;
-                while (k < hi) {
-                    const int mid = (k + hi) >> 1;
-                    if (my[mid * kRowThreads] < u)
-                        k = mid + 1;
-                    else
-                        hi = mid;
-                }
-                if (k < cnt && my[k * kRowThreads] == u) continue;   // already listed
-                if (cnt == kRowCap) {
-                    over = true;
-                    continue;
-                }
-                for (int j = cnt; j > k; --j) my[j * kRowThreads] = my[(j - 1) * kRowThreads];
-                my[k * kRowThreads] = u;
-                ++cnt;
+            for (int k = 0; k < N; ++k) f[k & 3] |= s[k] == u;
+            const bool found = (f[0] | f[1]) | (f[2] | f[3]);
+            if (__ballot(!found) == 0) continue;   // nothing new in the wave
+            u = found ? kNone : u;
+            // s'[k] = the median of s[k - 1] <= s[k] and u (kNone changes nothing;
+            // a full list drops its last entry)
+#pragma unroll
+            for (int k = N - 1; k > 0; --k) asm("v_med3_u32 %0, %1, %2, %0" : "+v"(s[k]) : "v"(s[k - 1]), "v"(u));
+            s[0] = min(s[0], u);
+        }
+}
+
+// The list of point r from its incidence list, eight cells at a time: their
+// loads are issued together (a cell past the end repeats the last one, whose
+// points are then found).
+template <int K, int N>
+__device__ inline void collect_row(const int32_t* __restrict__ cells, const int32_t* __restrict__ inc, uint32_t cap,
+                                   uint32_t p0, uint32_t p1, uint32_t r, uint32_t (&s)[N])
+{
+    constexpr int kBatch = 8;
+    constexpr uint32_t kCap = K == 4 ? kIncCap3 : kIncCap2;
+    s[0] = r;
+#pragma unroll
+    for (int k = 1; k < N; ++k) s[k] = kNone;
+    if (p1 <= p0) return;
+    if (cap == kCap) {
+        // a fixed list, 64 or 128 bytes a lane: read whole, before the cells are.
+        // (Read in eights between the gathers, the lists' lines left L2, where
+        // up to 24 points share a cell, before they were used up: 1.0 GB fetched
+        // instead of 0.46.)
+        typedef int32_t int4v __attribute__((ext_vector_type(4), aligned(4)));   // a caller's workspace may be unaligned
+        int32_t c[kCap];
+        const int4v* src = reinterpret_cast<const int4v*>(inc + p0);
+#pragma unroll
+        for (uint32_t q = 0; q < kCap / 4; ++q) {
+            const int4v w = src[q];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c[4 * q + e] = w[e];
+        }
+        const uint32_t m = p1 - p0;
+#pragma unroll
+        for (uint32_t g = 0; g < kCap; g += kBatch)
+            if (__ballot(g < m) != 0) {
+                int32_t b[kBatch];
+#pragma unroll
+                for (int q = 0; q < kBatch; ++q) b[q] = g + q < m ? c[g + q] : c[0];
+                collect_cells<K, N>(cells, b, s);
             }
+        return;
     }
-    if (over) longs[atomicAdd(n_long, 1u)] = (uint32_t)r;
-    deg[r] = over ? 0u : (uint32_t)cnt;
-    if (!over)
-        for (int k = 0; k < cnt; ++k) store[k * n + r] = my[k * kRowThreads];
+    for (uint32_t p = p0; p < p1; p += kBatch) {
+        int32_t b[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) b[q] = inc[min(p + q, p1 - 1)];
+        collect_cells<K, N>(cells, b, s);
+    }
+}
+
+// The list (less the point itself) to its place; false when it filled up.
+template <int N>
+__device__ inline bool keep_row(const uint32_t (&s)[N], int64_t n, int64_t r, uint32_t* __restrict__ deg,
+                                int32_t* __restrict__ store)
+{
+    if (s[N - 1] != kNone) return false;
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int k = 1; k < N; ++k) cnt += s[k] != kNone ? 1u : 0u;
+    deg[r] = cnt;
+#pragma unroll
+    for (int k = 0; k < N - 1; ++k)
+        if ((uint32_t)k < cnt) store[k * n + r] = (int32_t)(s[k] < (uint32_t)r ? s[k] : s[k + 1]);
+    return true;
+}
+
+// (Occupancy: 124 and 84 registers; with the scheduler's own choice it hoists
+// loads until two waves fit a SIMD, with more waves L2 holds fewer of the cells.)
+template <int K>
+__global__ void __launch_bounds__(kRowThreads) __attribute__((amdgpu_waves_per_eu(K == 4 ? 4 : 5)))
+ring_rows(const int32_t* __restrict__ cells, const int32_t* __restrict__ inc, const uint32_t* __restrict__ off,
+          const uint32_t* __restrict__ capp, int64_t n, uint32_t* __restrict__ deg, int32_t* __restrict__ store,
+          uint32_t* __restrict__ longs, uint32_t* __restrict__ n_long)
+{
+    static_assert(kRowCap == 32, "the stored lists hold what a list of 32 registers does");
+    // XCD-contiguous rows
+    const int64_t r = (int64_t)xcd_tile((int)blockIdx.x, (int)gridDim.x) * kRowThreads + threadIdx.x;
+    if (r >= n) return;
+    const uint32_t cap = *capp;
+    const IncRange ir = inc_range(off, cap, r);
+    bool done = false;
+    if (__ballot(ir.p1 - ir.p0 > (K == 4 ? 24u : 14u)) == 0) {
+        uint32_t s[16];
+        collect_row<K, 16>(cells, inc, cap, ir.p0, ir.p1, (uint32_t)r, s);
+        done = keep_row<16>(s, n, r, deg, store);
+    }
+    if (!done) {
+        uint32_t s[kRowCap];
+        collect_row<K, kRowCap>(cells, inc, cap, ir.p0, ir.p1, (uint32_t)r, s);
+        if (!keep_row<kRowCap>(s, n, r, deg, store)) {
+            longs[atomicAdd(n_long, 1u)] = (uint32_t)r;
+            deg[r] = 0;
+        }
+    }
 }
 
 // The stored lists into place: col[row_ptr[r] + k] = store[k * n + r] for the
-// rows ring_rows kept (a long row's count, set by long_rows, exceeds kRowCap).
+// rows ring_rows kept (a long row's count, set by long_rows, exceeds kRowCap - 2).
 // A workgroup's 256 rows are one contiguous stretch of col: each lane puts its
 // row into that stretch in LDS (long rows' entries marked -1), then the
 // stretch goes out with consecutive lanes writing consecutive entries.  A
@@ -359,7 +439,7 @@ __global__ void __launch_bounds__(256) copy_rows(const int32_t* __restrict__ sto
     const int64_t base = row_ptr[r0], total = row_ptr[r1] - base;
     const bool live = r < n;
     const uint32_t d = live ? deg[r] : 0u;
-    const bool kept = d <= (uint32_t)kRowCap;
+    const bool kept = d <= (uint32_t)kRowCap - 2;
     if (total > kCopySeg) {   // workgroup-uniform
         if (live && kept) {
             int32_t* out = col + row_ptr[r];

@@ -57,6 +57,39 @@ def test_ring1_csr_edge_cases():
         assert e.value.status == 2   # FTLE_ERR_BAD_MESH
 
 
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("m", [12, 13, 14, 15, 16, 17, 24, 25, 28, 29, 30, 31, 32, 33, 40])
+def test_ring1_csr_list_lengths(dim, m):
+    """Every length at which a point's list changes its form: fans of m triangles
+    closed around a point (m neighbours from m cells) and of m tetrahedra closed
+    around an edge (m + 1 neighbours, more than a ball of m tetrahedra would
+    give), many of them side by side so that waves mix them with short rows, in
+    a scattered numbering and with the cells in random order."""
+    rng = np.random.default_rng(100 * dim + m)
+    hubs, per = 70, m + dim - 1
+    n = hubs * per
+    number = rng.permutation(n)
+    cells = []
+    for h in range(hubs):
+        p = number[h * per:(h + 1) * per]
+        ring = p[dim - 1:]
+        for k in range(m if h % 3 else m - 2):   # every third one open
+            cells.append(list(p[:dim - 1]) + [ring[k], ring[(k + 1) % m]])
+    assert_same(dim, n, np.array(cells, np.int32)[rng.permutation(len(cells))])
+
+
+def test_ring1_csr_unaligned_workspace():
+    x, cells = meshes.kuhn_tet_grid(9)
+    n = x.shape[0]
+    c = torch.as_tensor(cells, device=DEV)
+    need = F.ring1_workspace_bytes(3, n, len(cells))
+    ws = torch.empty(need + 64, dtype=torch.uint8, device=DEV)
+    want = F.ring1_csr(3, n, c)
+    for off in (0, 8, 24):
+        got = F.ring1_csr(3, n, c, workspace=ws[off:off + need])
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
 def test_ring1_csr_capacity_reported():
     """Through the C ABI: too small a col_capacity fails with the count needed."""
     x, cells = meshes.jittered_tri_grid(6, 5, seed=1)
