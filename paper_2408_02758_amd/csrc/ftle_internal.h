@@ -227,6 +227,8 @@ size_t scan_partial_bytes(int64_t m);
 // maps to q = clamp(floor(((x_d - lo_d) / unit_d + 0.2) * scale), 0, qmax),
 // shifted up shift_bits when d is not the caller-order axis `fast` (>= 0),
 // and the axes' bits are interleaved (axis d at bit positions d, d + dim, ...).
+// For points numbered as a lattice q is the lattice index i / stride_d % size_d
+// of caller point i (size 0: no lattice).
 struct MortonParams {
     double lo[3];
     double unit[3];
@@ -234,6 +236,7 @@ struct MortonParams {
     double qmax;
     int fast;       // caller-order axis, or -1
     int shift_bits;
+    uint32_t stride[3], size[3];
 };
 
 // The mesh build on the device (ftle_meshbuild.hip).  Each launcher returns
@@ -241,10 +244,15 @@ struct MortonParams {
 //   mb_bbox: per-workgroup minima and maxima (part[b * 2 dim + d], then the
 //     maxima at + dim) over nblocks workgroups; *first_bad (set to ~0 before)
 //     gets the lowest point with a coordinate that is not finite
+//   mb_wraps: lohi, the bounds (dim minima, dim maxima) from mb_bbox's parts,
+//     and wraps (2 dim values, zeroed before): of the caller's steps i -> i + 1
+//     back along axis d by more than half its span the number and the sum of
+//     (i + 1)^2
 //   mb_order_counts: counts (3 dim values, zeroed before) of a sample of m
 //     steps between consecutive caller points, for the caller-order axis test
-//   mb_morton: codes key[i] and values val[i] = i, by `axis` (its fast axis
-//     found from the counts) where the caller's order has one, else by `plain`
+//   mb_morton: codes key[i] and values val[i] = i, by `plain` if it is a
+//     lattice's or (from the counts) the caller's order has no axis, else by
+//     `axis`
 //   mb_sort: stable sort of (key, val) by the low key_bits bits of key;
 //     *sorted_val is val or a buffer inside scratch (mb_sort_scratch_bytes)
 //   mb_invert: inv[perm[r]] = r
@@ -259,6 +267,8 @@ struct MortonParams {
 //   mb_normal_inverse: the 3D inverse normal matrices (caller order)
 hipError_t mb_bbox(int dim, bool f64, const void* x, int64_t n, double* part, int nblocks,
                    unsigned long long* first_bad, hipStream_t s);
+hipError_t mb_wraps(int dim, bool f64, const void* x, int64_t n, const double* part, int nblocks, double* lohi,
+                    unsigned long long* wraps, hipStream_t s);
 hipError_t mb_order_counts(int dim, bool f64, const void* x, int64_t m, int64_t stride, const MortonParams& mp,
                            uint32_t* counts, hipStream_t s);
 hipError_t mb_morton(int dim, bool f64, const void* x, int64_t n, const MortonParams& plain, const MortonParams& axis,

@@ -12,7 +12,9 @@
 // byte for byte.
 //
 //   bbox_partial    per-workgroup bounds of the coordinates (and whether all
-//                   are finite), reduced on the host
+//                   are finite)
+//   bbox_reduce / count_wraps
+//                   their reduction, and the ends of a lattice's rows and planes
 //   order_counts    the caller-order axis test, by counts of a sample's steps
 //   morton_keys     each point's interleaved code, quantised as the host
 //                   quantises it
@@ -144,6 +146,65 @@ __device__ inline int order_axis(const uint32_t* counts, int64_t m)
     return f;
 }
 
+// The bounds from all workgroups' partial ones (one workgroup).
+template <int D>
+__global__ void __launch_bounds__(256) bbox_reduce(const double* __restrict__ part, int nblocks,
+                                                   double* __restrict__ lohi)
+{
+    __shared__ double s[2 * D][256];
+    const int t = (int)threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < 2 * D; ++q) {
+        double v = q < D ? INFINITY : -INFINITY;
+        for (int b = t; b < nblocks; b += 256) {
+            const double u = part[(int64_t)b * 2 * D + q];
+            v = q < D ? fmin(v, u) : fmax(v, u);
+        }
+        s[q][t] = v;
+    }
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if (t < h)
+#pragma unroll
+            for (int q = 0; q < 2 * D; ++q) s[q][t] = q < D ? fmin(s[q][t], s[q][t + h]) : fmax(s[q][t], s[q][t + h]);
+        __syncthreads();
+    }
+    if (t < 2 * D) lohi[t] = s[t][0];
+}
+
+// The steps i -> i + 1 between consecutive caller points that go back along an
+// axis by more than half its span (the ends of a lattice's rows and planes):
+// wraps[2 d] their number and wraps[2 d + 1] the sum of their (i + 1)^2, modulo
+// 2^64.
+template <int D, typename T>
+__global__ void __launch_bounds__(256) count_wraps(const T* __restrict__ x, int64_t n, const double* __restrict__ lohi,
+                                                   unsigned long long* __restrict__ wraps)
+{
+    __shared__ unsigned long long c[2 * D];
+    const int t = (int)threadIdx.x;
+    if (t < 2 * D) c[t] = 0;
+    __syncthreads();
+    double back[D];
+    unsigned long long mine[2 * D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        back[d] = -0.5 * (lohi[D + d] - lohi[d]);
+        mine[2 * d] = mine[2 * d + 1] = 0;
+    }
+    for (int64_t i = (int64_t)blockIdx.x * 256 + t; i + 1 < n; i += (int64_t)gridDim.x * 256)
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if ((double)x[(i + 1) * D + d] - (double)x[i * D + d] < back[d]) {
+                mine[2 * d] += 1;
+                mine[2 * d + 1] += (unsigned long long)(i + 1) * (unsigned long long)(i + 1);
+            }
+#pragma unroll
+    for (int q = 0; q < 2 * D; ++q)
+        if (mine[q]) atomicAdd(&c[q], mine[q]);
+    __syncthreads();
+    if (t < 2 * D && c[t]) atomicAdd(&wraps[t], c[t]);
+}
+
 __device__ inline uint64_t spread2(uint64_t v)
 {
     v &= 0xffffffffULL;
@@ -166,8 +227,9 @@ __device__ inline uint64_t spread3(uint64_t v)
     return v;
 }
 
-// Codes by the parameters for the caller's order axis that the counts of m
-// samples show: plain, or (axis) with the other axes moved up.
+// Codes by `plain` if it is a lattice's, else by the parameters for the
+// caller's order axis that the counts of m samples show: plain, or (axis) with
+// the other axes moved up.
 template <int D, typename T>
 __global__ void __launch_bounds__(256) morton_keys(const T* __restrict__ x, int64_t n, MortonParams plain,
                                                    MortonParams axis, const uint32_t* __restrict__ counts, int64_t m,
@@ -176,14 +238,22 @@ __global__ void __launch_bounds__(256) morton_keys(const T* __restrict__ x, int6
 #pragma clang fp contract(off)
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    const int fast = order_axis<D>(counts, m);
-    MortonParams mp = fast >= 0 ? axis : plain;
-    mp.fast = fast;
+    MortonParams mp = plain;
+    if (!plain.size[0]) {
+        const int fast = order_axis<D>(counts, m);
+        if (fast >= 0) mp = axis;
+        mp.fast = fast;
+    }
     uint64_t code = 0;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        const double t = floor((((double)x[i * D + d] - mp.lo[d]) / mp.unit[d] + 0.2) * mp.scale);
-        uint64_t q = (uint64_t)fmin(mp.qmax, fmax(0.0, t));
+        uint64_t q;
+        if (mp.size[0]) {
+            q = (uint32_t)i / mp.stride[d] % mp.size[d];
+        } else {
+            const double t = floor((((double)x[i * D + d] - mp.lo[d]) / mp.unit[d] + 0.2) * mp.scale);
+            q = (uint64_t)fmin(mp.qmax, fmax(0.0, t));
+        }
         if (mp.fast >= 0 && d != mp.fast) q <<= mp.shift_bits;
         code |= (D == 2 ? spread2(q) : spread3(q)) << d;
     }
@@ -1006,6 +1076,25 @@ hipError_t mb_bbox(int dim, bool f64, const void* x, int64_t n, double* part, in
                    unsigned long long* first_bad, hipStream_t s)
 {
 #define FTLE_MB(D, T) hipLaunchKernelGGL((bbox_partial<D, T>), dim3(nblocks), dim3(256), 0, s, static_cast<const T*>(x), n, part, first_bad)
+    if (dim == 2) {
+        if (f64) FTLE_MB(2, double); else FTLE_MB(2, float);
+    } else {
+        if (f64) FTLE_MB(3, double); else FTLE_MB(3, float);
+    }
+#undef FTLE_MB
+    return hipGetLastError();
+}
+
+hipError_t mb_wraps(int dim, bool f64, const void* x, int64_t n, const double* part, int nblocks, double* lohi,
+                    unsigned long long* wraps, hipStream_t s)
+{
+    if (dim == 2)
+        hipLaunchKernelGGL(bbox_reduce<2>, dim3(1), dim3(256), 0, s, part, nblocks, lohi);
+    else
+        hipLaunchKernelGGL(bbox_reduce<3>, dim3(1), dim3(256), 0, s, part, nblocks, lohi);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+#define FTLE_MB(D, T) hipLaunchKernelGGL((count_wraps<D, T>), dim3(nblocks), dim3(256), 0, s, static_cast<const T*>(x), n, lohi, wraps)
     if (dim == 2) {
         if (f64) FTLE_MB(2, double); else FTLE_MB(2, float);
     } else {

@@ -9,6 +9,7 @@ arguments; and since every later call reads only those, the FTLE of both
 meshes agrees bit for bit (the 3D tape forward also reads the inverse normal
 matrices, formed on each side in float64 without contraction)."""
 import ctypes
+import itertools
 
 import numpy as np
 import pytest
@@ -496,3 +497,77 @@ def test_mesh_memory_is_reused_and_bounded():
     del again
     F.release_cached_memory()
     assert F.cached_memory_bytes() == 0
+
+
+def _lattice(dims, order, jitter, seed=5):
+    """A lattice of dims[d] points along axis d, its points numbered with the axes `order` from
+    the slowest to the fastest, and its Kuhn cells."""
+    dim = len(dims)
+    idx = np.stack(np.meshgrid(*[np.arange(dims[d]) for d in order], indexing="ij"), -1).reshape(-1, dim)
+    ijk = np.empty_like(idx)
+    ijk[:, list(order)] = idx
+    stride = np.empty(dim, np.int64)
+    stride[list(order)] = [int(np.prod([dims[o] for o in order[k + 1:]])) for k in range(dim)]
+    x = ijk * np.linspace(1.0, 0.7, dim) + np.random.default_rng(seed).uniform(-jitter, jitter, ijk.shape)
+    base = np.flatnonzero(np.all(ijk < np.array(dims) - 1, 1))
+    cells = []
+    for p in itertools.permutations(range(dim)):
+        at, c = base.copy(), [base]
+        for d in p:
+            at = at + stride[d]
+            c.append(at)
+        cells.append(np.stack(c, 1))
+    return x, np.concatenate(cells).astype(np.int32), ijk
+
+
+def _block_sizes(ijk, fast, limit):
+    """The lattice's points in the order of their interleaved indices (the axes but `fast` one bit
+    up), cut at the highest bit that differs until a run holds at most `limit`."""
+    dim = ijk.shape[1]
+    code = np.zeros(len(ijk), np.int64)
+    for d in range(dim):
+        q = ijk[:, d].astype(np.int64) << (0 if d == fast else 1)
+        for b in range(16):
+            code |= (q >> b & 1) << (dim * b + d)
+    code.sort()
+    todo, sizes = [code], []
+    while todo:
+        c = todo.pop()
+        if len(c) <= limit:
+            sizes.append(len(c))
+            continue
+        top = int(c[0] ^ c[-1]).bit_length() - 1
+        cut = int(np.searchsorted(c, c[-1] >> top << top))
+        todo += [c[:cut], c[cut:]]
+    return sizes
+
+
+@pytest.mark.parametrize("dims,order,jitter,tile_log2", [
+    ((2, 2), (0, 1), 0.0, 0),            # the smallest
+    ((65, 33), (1, 0), 0.0, 9),          # one row and one column past whole blocks, x fastest
+    ((33, 130), (0, 1), 0.2, 8),         # jittered, y fastest
+    ((9, 17, 33), (0, 1, 2), 0.0, 6),    # one plane past whole blocks on each axis
+    ((31, 11, 13), (2, 1, 0), 0.2, 7),
+    ((12, 40, 7), (0, 2, 1), 0.0, 5),    # the middle axis fastest
+])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_lattice_blocks(dims, order, jitter, tile_log2, dtype):
+    # a lattice stored row by row: tiles are blocks of its points, on the host and on the device
+    x, cells, ijk = _lattice(dims, order, jitter)
+    _, dev = assert_same_mesh(x, cells, dtype, tile_log2=tile_log2)
+    sizes = _block_sizes(ijk, order[-1], 1 << (tile_log2 or 9))
+    st = dev.tile_stats()
+    assert st["n_tiles"] == len(sizes) and st["max_tile_points"] == max(sizes)
+
+
+@pytest.mark.parametrize("dims", [(40, 23), (9, 10, 11)])
+def test_almost_a_lattice(dims):
+    # two far points exchanged, a row left out: the general order, still as the host builds it
+    x, cells, ijk = _lattice(dims, tuple(range(len(dims))), 0.0)
+    n = len(x)
+    to = np.arange(n)
+    to[[5, n - 7]] = to[[n - 7, 5]]
+    assert_same_mesh(x[to], to[cells].astype(np.int32))
+    drop = np.all(ijk[:, :-1] == 0, 1)
+    new = np.cumsum(~drop) - 1
+    assert_same_mesh(x[~drop], new[cells[~drop[cells].any(1)]].astype(np.int32))
