@@ -221,9 +221,15 @@ __global__ void __launch_bounds__(B) ell_kernel(const T* __restrict__ x, const T
     out[i] = f;
 }
 
+constexpr int kAhead = 4;   // neighbours of a row loaded together
+
 // The paper's list from a one-ring CSR, one lane per point, in float64 with
 // no contraction of products into FMAs (so that every comparison is the one
-// a plain float64 evaluation of the same formula makes).
+// a plain float64 evaluation of the same formula makes).  Bound by the gathers
+// (an index, then its coordinates) and by the float64 roots and divisions: a
+// row's neighbours are loaded kAhead at a time, and an axis takes one division
+// for both its sides (787k points in 2D 26.9 -> 24.2 us; the list call of 90^3
+// points in float64 378 -> 360 us; eight at a time measure the same).
 template <int D, typename T>
 __global__ void __launch_bounds__(256) axis_ell_kernel(const T* __restrict__ x, const int64_t* __restrict__ row_ptr,
                                                          const int32_t* __restrict__ col, int64_t n,
@@ -243,30 +249,40 @@ __global__ void __launch_bounds__(256) axis_ell_kernel(const T* __restrict__ x, 
         best_j[k] = -1;
         best_c[k] = 0.0;
     }
-    for (int64_t p = p0; p < p1; ++p) {
-        const int32_t j = col[p];
-        if ((uint64_t)(int64_t)j >= (uint64_t)n || j == i) continue;   // not a neighbour
-        double dx[D];
-        double nrm2 = 0.0;
+    for (int64_t p = p0; p < p1; p += kAhead) {
+        int32_t j[kAhead];
+        T v[kAhead][D];
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            dx[d] = (double)x[(int64_t)j * D + d] - xi[d];
-            nrm2 = nrm2 + dx[d] * dx[d];
+        for (int u = 0; u < kAhead; ++u) j[u] = p + u < p1 ? col[p + u] : (int32_t)i;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if ((uint64_t)(int64_t)j[u] >= (uint64_t)n) j[u] = (int32_t)i;   // not a neighbour: on no side
+#pragma unroll
+            for (int d = 0; d < D; ++d) v[u][d] = x[(int64_t)j[u] * D + d];
         }
-        const double nrm = sqrt(nrm2);
 #pragma unroll
-        for (int d = 0; d < D; ++d)
+        for (int u = 0; u < kAhead; ++u) {
+            double dx[D];
+            double nrm2 = 0.0;
 #pragma unroll
-            for (int sg = 0; sg < 2; ++sg) {
-                const double along = sg ? dx[d] : -dx[d];
-                if (!(along > 0.0)) continue;
-                const double c = along / nrm;
-                const int k = 2 * d + sg;
-                if (best_j[k] < 0 || c > best_c[k]) {   // rows ascend: ties keep the smaller index
-                    best_c[k] = c;
-                    best_j[k] = j;
+            for (int d = 0; d < D; ++d) {
+                dx[d] = (double)v[u][d] - xi[d];
+                nrm2 = nrm2 + dx[d] * dx[d];
+            }
+            const double nrm = sqrt(nrm2);
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const double c = fabs(dx[d]) / nrm;   // one division for both sides
+#pragma unroll
+                for (int sg = 0; sg < 2; ++sg) {
+                    const int k = 2 * d + sg;
+                    // rows ascend: ties keep the smaller index
+                    const bool take = (sg ? dx[d] : -dx[d]) > 0.0 && (best_j[k] < 0 || c > best_c[k]);
+                    best_c[k] = take ? c : best_c[k];
+                    best_j[k] = take ? j[u] : best_j[k];
                 }
             }
+        }
     }
     if constexpr (D == 2) {
         reinterpret_cast<int4*>(ell)[i] = int4{best_j[0], best_j[1], best_j[2], best_j[3]};
