@@ -957,6 +957,7 @@ __global__ void __launch_bounds__(256) axis_slots(const T* __restrict__ x, const
             const double nrm = sqrt(nrm2);
 #pragma unroll
             for (int d = 0; d < D; ++d) {
+                if (dx[d] == 0.0) continue;            // on no side (whole waves on a lattice)
                 const double cs = fabs(dx[d]) / nrm;   // one division for both sides
 #pragma unroll
                 for (int sg = 0; sg < 2; ++sg) {
