@@ -175,3 +175,25 @@ def test_ring1_csr_too_long_a_row_is_unsupported():
     with pytest.raises(F.FTLEError) as e:
         device_ring1(2, 2 * m + 1, star)
     assert e.value.status == 4 and "4096" in e.value.message
+
+
+@pytest.mark.parametrize("nx,ny", [
+    (64, 32),        # one tile of the row-pointer scan, full
+    (683, 3),        # one row past it
+    (2048, 4096),    # the most tiles whose workgroups add up the sums before them
+    (2897, 2897),    # past that: the tiles' sums are scanned in between
+])
+def test_row_pointers_over_scan_sizes(nx, ny):
+    n = nx * ny
+    i = torch.arange(n, device=DEV).reshape(ny, nx)
+    a, b, c, d = (t.reshape(-1) for t in (i[:-1, :-1], i[:-1, 1:], i[1:, :-1], i[1:, 1:]))
+    cells = torch.cat([torch.stack([a, b, d], 1), torch.stack([a, d, c], 1)]).to(torch.int32)
+    rp, col = F.ring1_csr(2, n, cells)
+    y, x = i.reshape(-1) // nx, i.reshape(-1) % nx
+    ok, nb = [], []
+    for dy, dx in ((-1, -1), (-1, 0), (0, -1), (0, 1), (1, 0), (1, 1)):   # ascending
+        ok.append((x + dx >= 0) & (x + dx < nx) & (y + dy >= 0) & (y + dy < ny))
+        nb.append(i.reshape(-1) + dy * nx + dx)
+    ok, nb = torch.stack(ok, 1), torch.stack(nb, 1)
+    assert torch.equal(rp[1:], ok.sum(1).cumsum(0)) and int(rp[0]) == 0
+    assert torch.equal(col.to(torch.int64), nb[ok])
