@@ -80,10 +80,10 @@ enum {
     FTLE_HOST_ONLY = 1 << 5
 };
 /* Points per tile (one workgroup's share): FTLE_TILE(k) asks for 2^k points,
- * 5 <= k <= 11; 0 selects the default, 512.  Points numbered as a lattice row
- * by row are cut into blocks of at most that many.  A tile is halved until its own
- * and halo points fit 1024 staged slots and 64 KiB of LDS (96 KiB in 3D
- * float64). */
+ * 5 <= k <= 11; 0 selects the default, 512.  In 3D, points numbered as a
+ * lattice row by row are cut into blocks of at most that many.  A tile is
+ * halved until its own and halo points fit 1024 staged slots and 64 KiB of LDS
+ * (96 KiB in 3D float64). */
 #define FTLE_TILE(k) ((unsigned)(k) << 8)
 
 /*

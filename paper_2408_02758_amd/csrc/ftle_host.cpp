@@ -974,15 +974,9 @@ Lattice lattice_from_wraps(int dim, int64_t n, const unsigned long long* wraps)
     return lat;
 }
 
-// The nominal chunks of a lattice's points in Morton order: the box of all
-// points is halved by the codes' bits from the highest (bit k of axis d at
-// place dim (k + 1) + d, of the fast axis at dim k + d) until a box holds at
-// most tile_points.  Runs of tile_points would straddle the blocks wherever a
-// size is no multiple of a block's, and a straddling chunk's halo is up to
-// twice a block's: in 3D most such chunks outgrow the staging and are halved
-// again.  127 x 113 x 101: 5502 tiles of 264 points, by blocks 2962 of 489, and
-// the forward 25.6 -> 21.3 us (f64 58.6 -> 43.5, axis stencil 20.6 -> 16.0,
-// 189 x 151 x 137 74.0 -> 58.7); 2000 x 1990 31.3 -> 29.6 us.
+// A lattice's points in Morton order in blocks: the box of all points is halved
+// by the codes' bits from the highest (bit k of axis d at place dim (k + 1) + d,
+// of the fast axis at dim k + d) until a box holds at most tile_points.
 std::vector<Chunk> lattice_chunks(int dim, const Lattice& lat, int tile_points)
 {
     struct Box {
@@ -1023,9 +1017,18 @@ std::vector<Chunk> lattice_chunks(int dim, const Lattice& lat, int tile_points)
     return out;
 }
 
+// The nominal chunks: runs of tile_points, and for lattices in 3D blocks.  Runs
+// straddle the blocks wherever a size is no multiple of a block's, and a
+// straddling run's halo is up to twice a block's: in 3D most such runs outgrow
+// the staging and are halved again.  127 x 113 x 101: 5502 tiles of 264 points,
+// by blocks 2962 of 489, and the forward 25.6 -> 21.2 us (f64 58.6 -> 42.9, axis
+// stencil 20.6 -> 15.9, 189 x 151 x 137 74.0 -> 55.5).  In 2D no run is halved,
+// and blocks, some of them thin, are more tiles for the same points: 32 meshes
+// of 100^2 to 500^2 in one launch 21.2 us by blocks, 21.0 by runs (2301 x 1651
+// alone 28.4 and 28.8; ordered without the lattice 29.4).
 std::vector<Chunk> nominal_chunks(int dim, int64_t n, const Lattice& lat, int tile_points)
 {
-    return lat.fast >= 0 ? lattice_chunks(dim, lat, tile_points) : even_chunks(n, tile_points);
+    return lat.fast >= 0 && dim == 3 ? lattice_chunks(dim, lat, tile_points) : even_chunks(n, tile_points);
 }
 
 // Quantise each axis in units of the mean point spacing, with `sub`

@@ -552,10 +552,12 @@ def _block_sizes(ijk, fast, limit):
 ])
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 def test_lattice_blocks(dims, order, jitter, tile_log2, dtype):
-    # a lattice stored row by row: tiles are blocks of its points, on the host and on the device
+    # a lattice stored row by row: its tiles are blocks of its points in 3D and runs of its codes
+    # in 2D, on the host and on the device
     x, cells, ijk = _lattice(dims, order, jitter)
     _, dev = assert_same_mesh(x, cells, dtype, tile_log2=tile_log2)
-    sizes = _block_sizes(ijk, order[-1], 1 << (tile_log2 or 9))
+    limit = 1 << (tile_log2 or 9)
+    sizes = _block_sizes(ijk, order[-1], limit) if len(dims) == 3 else [min(limit, len(x))] * -(-len(x) // limit)
     st = dev.tile_stats()
     assert st["n_tiles"] == len(sizes) and st["max_tile_points"] == max(sizes)
 
