@@ -1703,7 +1703,8 @@ ftle_mesh_t build_mesh_device(int dim, int64_t n, const void* coords, ftle_dtype
         {
             void* ws = arena.take<void>(ring1_workspace_bytes(dim, n, n_cells));
             int bad_mesh = 0, too_long = 0;
-            check_hip(ring1_build(dim, mc, n_cells, n, ws, rp, nullptr, 0, &nnz, &bad_mesh, &too_long, s),
+            bool any_long = false;
+            check_hip(ring1_build(dim, mc, n_cells, n, ws, rp, nullptr, 0, &nnz, &bad_mesh, &too_long, &any_long, s),
                       "one-ring stencil kernels");
             if (bad_mesh) fail(FTLE_ERR_DEVICE, "relabelled cells failed the stencil's range check");
             if (too_long) fail(FTLE_ERR_UNSUPPORTED, "a point's incident cells list more than 4096 points");
@@ -1715,7 +1716,7 @@ ftle_mesh_t build_mesh_device(int dim, int64_t n, const void* coords, ftle_dtype
                 m->d_col = static_cast<int32_t*>(dev_upload(nullptr, (size_t)nnz * 4));
                 colp = m->d_col;
             }
-            if (nnz) check_hip(ring1_write(dim, mc, n_cells, n, ws, rp, colp, s), "one-ring stencil kernels");
+            if (nnz) check_hip(ring1_write(dim, mc, n_cells, n, ws, rp, colp, any_long, s), "one-ring stencil kernels");
             check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
         }
         if (axis) {
@@ -2635,9 +2636,10 @@ void ring1_run(int dim, int64_t n_points, int64_t n_cells, const int32_t* cells,
                int64_t col_capacity, int64_t* nnz, void* workspace, hipStream_t s)
 {
     int bad = 0, too_long = 0;
+    bool any_long = false;
     int64_t count = 0;
     check_hip(ring1_build(dim, cells, n_cells, n_points, workspace, row_ptr, col, col_capacity, &count, &bad,
-                          &too_long, s),
+                          &too_long, &any_long, s),
               "one-ring stencil");
     if (bad) fail(FTLE_ERR_BAD_MESH, "cell index outside [0, n_points)");
     if (too_long) fail(FTLE_ERR_UNSUPPORTED, "a point's incident cells list more than 4096 points");

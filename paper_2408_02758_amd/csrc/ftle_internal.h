@@ -211,13 +211,14 @@ hipError_t launch_advect(int kind, const double* params, bool f64, int64_t n, co
 // otherwise *nnz holds the entry count, and row_ptr / col are written when it
 // is at most col_capacity.  Synchronises the stream.
 // col = NULL: count only (row_ptr written, nothing else); ring1_write then
-// writes col from the same workspace.
+// writes col from the same workspace, given *any_long (whether the list of
+// long rows has any).
 size_t ring1_workspace_bytes(int dim, int64_t n, int64_t n_cells);
 hipError_t ring1_build(int dim, const int32_t* cells, int64_t n_cells, int64_t n, void* workspace, int64_t* row_ptr,
                        int32_t* col, int64_t col_capacity, int64_t* nnz, int* bad_mesh, int* too_long,
-                       hipStream_t stream);
+                       bool* any_long, hipStream_t stream);
 hipError_t ring1_write(int dim, const int32_t* cells, int64_t n_cells, int64_t n, void* workspace,
-                       const int64_t* row_ptr, int32_t* col, hipStream_t stream);
+                       const int64_t* row_ptr, int32_t* col, bool any_long, hipStream_t stream);
 // Exclusive scan of m uint32 values into out[0..m), out[m] = their sum
 // (in and out may coincide); partial: scan_partial_bytes(m) of device scratch.
 hipError_t scan_exclusive_u32(const uint32_t* in, int64_t m, uint32_t* out, uint32_t* partial, hipStream_t stream);

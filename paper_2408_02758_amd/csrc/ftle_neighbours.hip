@@ -221,7 +221,7 @@ __device__ inline Out lane_up(Out v, int by)
 
 template <typename Out>
 __global__ void __launch_bounds__(kScanThreads) scan_tiles(const uint32_t* in, int64_t m, Out* out,
-                                                             Out* __restrict__ partial)   // in and out may coincide
+                                                             Out* __restrict__ partial, Out* copy)   // in and out may coincide
 {
     constexpr int kPad = kScanItems + 1;   // a lane's items, one word apart from the next lane's
     __shared__ Out s[kScanThreads * kPad];
@@ -262,12 +262,16 @@ __global__ void __launch_bounds__(kScanThreads) scan_tiles(const uint32_t* in, i
     }
     if (tid == kScanThreads - 1) {
         partial[blockIdx.x] = incl;
-        if (gridDim.x == 1) out[m] = incl;
+        if (gridDim.x == 1) {
+            out[m] = incl;
+            if (copy) *copy = incl;
+        }
     }
 }
 
 template <typename Out>
-__global__ void __launch_bounds__(1024) scan_partials(Out* __restrict__ partial, int64_t np, Out* __restrict__ total)
+__global__ void __launch_bounds__(1024) scan_partials(Out* __restrict__ partial, int64_t np, Out* __restrict__ total,
+                                                      Out* copy)
 {
     __shared__ Out s[1024];
     const int tid = (int)threadIdx.x;
@@ -280,13 +284,16 @@ __global__ void __launch_bounds__(1024) scan_partials(Out* __restrict__ partial,
         carry += s[1023];
         __syncthreads();
     }
-    if (tid == 0) *total = carry;
+    if (tid == 0) {
+        *total = carry;
+        if (copy) *copy = carry;
+    }
 }
 
 // A workgroup per tile.
 template <typename Out, bool DIRECT>
 __global__ void __launch_bounds__(kScanThreads) add_partials(Out* __restrict__ out, int64_t m,
-                                                             const Out* __restrict__ partial)
+                                                             const Out* __restrict__ partial, Out* copy)
 {
     __shared__ Out wave_sum[kScanThreads / 64];
     const int tid = (int)threadIdx.x;
@@ -303,7 +310,10 @@ __global__ void __launch_bounds__(kScanThreads) add_partials(Out* __restrict__ o
         add = 0;
 #pragma unroll
         for (int w = 0; w < kScanThreads / 64; ++w) add += wave_sum[w];
-        if (tid == 0 && tile == (int64_t)gridDim.x - 1) out[m] = add + partial[tile];
+        if (tid == 0 && tile == (int64_t)gridDim.x - 1) {
+            out[m] = add + partial[tile];
+            if (copy) *copy = add + partial[tile];
+        }
     } else {
         add = partial[tile];
     }
@@ -320,21 +330,20 @@ __global__ void __launch_bounds__(kScanThreads) add_partials(Out* __restrict__ o
 // 41.4 / 47.7, 8192 82.6 / 88.8, 16384 268 / 208; uint32 at 8192 63.0 / 60.4).
 constexpr int64_t kDirectTiles = 4096;
 
+// copy: another place for the total, or null.
 template <typename Out>
-hipError_t exclusive_scan(const uint32_t* in, int64_t m, Out* out, Out* partial, hipStream_t stream)
+hipError_t exclusive_scan(const uint32_t* in, int64_t m, Out* out, Out* partial, hipStream_t stream,
+                          Out* copy = nullptr)
 {
     const int64_t tiles = (m + kScanTile - 1) / kScanTile;
-    if (tiles > 0)
-        hipLaunchKernelGGL((scan_tiles<Out>), dim3((unsigned)tiles), dim3(kScanThreads), 0, stream, in, m, out,
-                           partial);
+    const dim3 grid((unsigned)tiles), block(kScanThreads);
+    if (tiles > 0) hipLaunchKernelGGL((scan_tiles<Out>), grid, block, 0, stream, in, m, out, partial, copy);
     if (tiles > kDirectTiles || tiles == 0)
-        hipLaunchKernelGGL((scan_partials<Out>), dim3(1), dim3(1024), 0, stream, partial, tiles, out + m);
+        hipLaunchKernelGGL((scan_partials<Out>), dim3(1), dim3(1024), 0, stream, partial, tiles, out + m, copy);
     if (tiles > kDirectTiles)
-        hipLaunchKernelGGL((add_partials<Out, false>), dim3((unsigned)tiles), dim3(kScanThreads), 0, stream, out, m,
-                           (const Out*)partial);
+        hipLaunchKernelGGL((add_partials<Out, false>), grid, block, 0, stream, out, m, (const Out*)partial, copy);
     else if (tiles > 1)
-        hipLaunchKernelGGL((add_partials<Out, true>), dim3((unsigned)tiles), dim3(kScanThreads), 0, stream, out, m,
-                           (const Out*)partial);
+        hipLaunchKernelGGL((add_partials<Out, true>), grid, block, 0, stream, out, m, (const Out*)partial, copy);
     return hipGetLastError();
 }
 
@@ -623,7 +632,8 @@ uint32_t inc_cap(int dim, int64_t n)
 // counts and offsets (n + 1), cursors (n), incidence lists (the larger of
 // K n_cells packed and n fixed lists), distinct counts (n + 1), long rows
 // (n), stored lists (kRowCap n), scan partial sums, then the error flags,
-// the long-row count and the fixed list length in use (0: packed lists).
+// the long-row count, the fixed list length in use (0: packed lists) and a copy
+// of the entry count.
 struct Ring1Work {
     uint32_t *cnt, *cur, *deg, *longs, *n_long, *cap;
     int32_t *inc, *store;
@@ -669,7 +679,7 @@ size_t ring1_workspace_bytes(int dim, int64_t n, int64_t n_cells)
 
 hipError_t ring1_build(int dim, const int32_t* cells, int64_t n_cells, int64_t n, void* workspace, int64_t* row_ptr,
                        int32_t* col, int64_t col_capacity, int64_t* nnz, int* bad_mesh, int* too_long,
-                       hipStream_t stream)
+                       bool* any_long, hipStream_t stream)
 {
     const Ring1Work w = carve_ring1(workspace, dim, n, n_cells, nullptr);
     uint32_t* cnt = w.cnt;
@@ -680,11 +690,19 @@ hipError_t ring1_build(int dim, const int32_t* cells, int64_t n_cells, int64_t n
     void* partial = w.partial;
     int* err = w.err;
     uint32_t* n_long = w.n_long;
+    // what the host needs at the end, as it lies in the workspace
+    struct {
+        int flags;
+        uint32_t n_long, cap, pad;
+        int64_t total;
+    } end{};
+    static_assert(sizeof(end) == 24, "the counters' layout");
+    int64_t* total = reinterpret_cast<int64_t*>(err + 4);
     hipError_t e;
 #define FTLE_CHECK(x)                          \
     if ((e = (x)) != hipSuccess) return e;
     FTLE_CHECK(hipMemsetAsync(cnt, 0, 4 * (size_t)(n + 1), stream));
-    FTLE_CHECK(hipMemsetAsync(err, 0, 12, stream));   // flags, long rows, fixed list length
+    FTLE_CHECK(hipMemsetAsync(err, 0, 24, stream));
     const dim3 ag(blocks_for(n_cells, kAggThreads * kAggCells)), ab(kAggThreads);
     // 1. fixed lists (with the counts), or the counts alone
     const uint32_t cap = n_cells > 0 ? inc_cap(dim, n) : 0u;
@@ -702,14 +720,13 @@ hipError_t ring1_build(int dim, const int32_t* cells, int64_t n_cells, int64_t n
         }
         FTLE_CHECK(hipGetLastError());
     }
-    int flags = 0;
-    FTLE_CHECK(hipMemcpyAsync(&flags, err, sizeof(int), hipMemcpyDeviceToHost, stream));
+    FTLE_CHECK(hipMemcpyAsync(&end.flags, err, sizeof(int), hipMemcpyDeviceToHost, stream));
     FTLE_CHECK(hipStreamSynchronize(stream));
-    if (flags & 1) {
+    if (end.flags & 1) {
         *bad_mesh = 1;
         return hipSuccess;
     }
-    if (cap && !(flags & 4)) {
+    if (cap && !(end.flags & 4)) {
         // every list fits: the rows read them in place
         FTLE_CHECK(hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(w.cap), (int)cap, 1, stream));
     } else if (n_cells > 0) {
@@ -736,26 +753,30 @@ hipError_t ring1_build(int dim, const int32_t* cells, int64_t n_cells, int64_t n
                            n_long, deg, nullptr, nullptr, err);
     }
     FTLE_CHECK(hipGetLastError());
-    FTLE_CHECK(exclusive_scan<int64_t>(deg, n, row_ptr, static_cast<int64_t*>(partial), stream));
-    int64_t total = 0;
-    FTLE_CHECK(hipMemcpyAsync(&total, row_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
-    FTLE_CHECK(hipMemcpyAsync(&flags, err, sizeof(int), hipMemcpyDeviceToHost, stream));
+    FTLE_CHECK(exclusive_scan<int64_t>(deg, n, row_ptr, static_cast<int64_t*>(partial), stream, total));
+    // one copy of flags, long rows and total, and no long-row write where there
+    // are none: 1023 x 769 points 162 -> 152 us (a single wait, with the rows
+    // queued behind the lists and skipped on an error, gained 2 us and cost 25
+    // where a point's cells outgrow the fixed lists)
+    FTLE_CHECK(hipMemcpyAsync(&end, err, sizeof end, hipMemcpyDeviceToHost, stream));
     FTLE_CHECK(hipStreamSynchronize(stream));
-    *nnz = total;
-    if (flags & 2) {
+    *nnz = end.total;
+    *any_long = end.n_long != 0;
+    if (end.flags & 2) {
         *too_long = 1;
         return hipSuccess;
     }
-    if (!col || total > col_capacity || total == 0) return hipSuccess;
-    return ring1_write(dim, cells, n_cells, n, workspace, row_ptr, col, stream);
+    if (!col || end.total > col_capacity || end.total == 0) return hipSuccess;
+    return ring1_write(dim, cells, n_cells, n, workspace, row_ptr, col, *any_long, stream);
 #undef FTLE_CHECK
 }
 
 hipError_t ring1_write(int dim, const int32_t* cells, int64_t n_cells, int64_t n, void* workspace,
-                       const int64_t* row_ptr, int32_t* col, hipStream_t stream)
+                       const int64_t* row_ptr, int32_t* col, bool any_long, hipStream_t stream)
 {
     const Ring1Work w = carve_ring1(workspace, dim, n, n_cells, nullptr);
     hipLaunchKernelGGL(copy_rows, dim3(blocks_for(n)), dim3(256), 0, stream, w.store, n, w.deg, row_ptr, col);
+    if (!any_long) return hipGetLastError();
     if (dim == 2)
         hipLaunchKernelGGL((long_rows<3, true>), dim3(kLongGrid), dim3(256), 0, stream, cells, w.inc, w.cnt, w.cap, w.longs,
                            w.n_long, w.deg, row_ptr, col, w.err);

@@ -197,3 +197,22 @@ def test_row_pointers_over_scan_sizes(nx, ny):
     ok, nb = torch.stack(ok, 1), torch.stack(nb, 1)
     assert torch.equal(rp[1:], ok.sum(1).cumsum(0)) and int(rp[0]) == 0
     assert torch.equal(col.to(torch.int64), nb[ok])
+
+
+@pytest.mark.parametrize("n", [50, 5000])   # one tile of the row-pointer scan, several
+@pytest.mark.parametrize("fan", [False, True])
+def test_bad_index_writes_nothing(n, fan):
+    # an index outside [0, n), with and without a point whose cells outgrow the fixed lists, leaves
+    # the caller's arrays alone
+    i = np.arange(n - 2)
+    cells = np.stack([np.zeros_like(i) if fan else i, i + 1, i + 2], 1).astype(np.int32)
+    cells[n // 2, 2] = n
+    c = torch.as_tensor(cells, device=DEV)
+    row_ptr = torch.full((n + 1,), -7, dtype=torch.int64, device=DEV)
+    col = torch.full((6 * len(cells),), -7, dtype=torch.int32, device=DEV)
+    nnz = ctypes.c_int64(-7)
+    L = _lib.load()
+    rc = L.ftle_ring1_csr(2, n, len(cells), c.data_ptr(), row_ptr.data_ptr(), col.data_ptr(), col.numel(),
+                          ctypes.byref(nnz), torch.cuda.current_stream().cuda_stream)
+    assert rc != 0 and b"outside" in L.ftle_last_error()
+    assert bool((row_ptr == -7).all()) and bool((col == -7).all())
