@@ -56,36 +56,28 @@ __device__ inline void flow_velocity(const FlowParams& pr, const double* p, doub
 }
 
 // ---------------------------------------------------------------------------
-// The bounded path.  Particles whose whole path stays below kReach (bounded
-// once, before the first step, from x0, T and the largest velocity) take
-// steps with the sines and cosines written out below; the others (huge or
-// non-finite coordinates and parameters) take general_steps.
+// The bounded path.  Steps in which every argument stays below kReach (known
+// from the position, the time left and the largest velocity) take the sines and
+// cosines written out below; the others (huge or non-finite coordinates and
+// parameters) take flow_velocity's.
 //
 // A step is float64 instruction issue and nothing else, so the work per stage
 // decides.  The library's sincospi and sincos reduce to an eighth of a period
 // and evaluate both functions of each argument, with the swaps and signs of
 // eight octants.  Here:
-//  - the double gyre's products of a sine and a cosine are two sines,
-//      2 sin(pi f) cos(pi y) = sin(pi (f + y)) + sin(pi (f - y)),
-//      2 cos(pi f) sin(pi y) = sin(pi (f + y)) - sin(pi (f - y)),
-//    so a stage evaluates two odd polynomials on half a period instead of
-//    four on an eighth.  y is first reduced to y - rint(y) (exact), so that the
-//    sums carry no larger rounding than f itself and a particle on a wall (y an
-//    integer) gets a normal velocity of exactly zero;
+//  - the double gyre's four factors are odd polynomials on half a period: the
+//    sines of f - rint(f) and y - rint(y) (exact), the cosines of the distance
+//    to their own zero, 1/2 - |.|, and one sign for both products.  Odd
+//    polynomials keep a factor's relative exactness at its zero, so that a
+//    particle next to a wall leaves it as it should and one on a wall (y an
+//    integer, x = 0) has a normal velocity of exactly zero.  (Two sines of
+//    f + y and f - y would do, but their sum and difference cancel there.);
 //  - the ABC flow's six values come from three reductions to half a period
 //    (argument - k pi, pi in two parts), one sine and one cosine polynomial each
 //    with the sign (-1)^k, no octant selects;
 //  - the scale factors of the velocity are folded into the steps' h and h/6.
-// The polynomials are Chebyshev economisations of the Taylor series with nine
-// terms (gen_sincos_poly.py; dropped terms below 4e-18), so a velocity is as
-// exact as the library's forms make it: about one rounding of the argument and
-// one of the result, far below the rounding of the position, which a step
-// makes once (80-bit reference, 4000 particles: rms error 1.4e-15 against
-// 1.6e-15 over T = 5, 5.9e-14 against 5.8e-14 over T = 15).
-// Vector instructions per step: double gyre 188 (library forms 435), ABC 359
-// (778), all issued back to back (4.2 cycles each).  1024 x 512 particles, 1500
-// double-gyre steps, float32: 3.94 ms (8.87); 81 x 67 x 59 particles, 500 ABC
-// steps, float64: 1.56 ms (3.54).
+// The polynomials are Chebyshev economisations of the Taylor series
+// (gen_sincos_poly.py; dropped terms below 4e-18).
 // ---------------------------------------------------------------------------
 constexpr double kReach = 1073741824.0;   // 2^30: periods fit the 32-bit parity below
 
@@ -95,22 +87,19 @@ __device__ inline double flip_sign(double v, uint32_t parity)
     return __longlong_as_double(__double_as_longlong(v) ^ (long long)((unsigned long long)(parity << 31) << 32));
 }
 
-// sin(pi (c - rint(c))) (-1)^(rint(c) + parity)
-__device__ inline double sin_pi(double c, uint32_t parity)
+// sin(pi r) / pi, |r| <= 1/2
+__device__ inline double half_sine(double r)
 {
-#pragma clang fp contract(off)
-    const double k = rint(c);
-    const double r = c - k, z = r * r;
-    double s = 7.697847275590284e-07;
-    s = __builtin_fma(s, z, -2.1903499125519212e-05);
-    s = __builtin_fma(s, z, 0.00046629981702308817);
-    s = __builtin_fma(s, z, -0.007370430506093225);
-    s = __builtin_fma(s, z, 0.08214588657312355);
-    s = __builtin_fma(s, z, -0.599264529318946);
-    s = __builtin_fma(s, z, 2.5501640398773007);
-    s = __builtin_fma(s, z, -5.167712780049969);
-    s = __builtin_fma(s, z, 3.141592653589793);
-    return flip_sign(r, (uint32_t)(int)k + parity) * s;
+    const double z = r * r;
+    double s = 2.45918692848767e-07;
+    s = __builtin_fma(s, z, -6.972961128185442e-06);
+    s = __builtin_fma(s, z, 0.00014842817836379502);
+    s = __builtin_fma(s, z, -0.002346080963525959);
+    s = __builtin_fma(s, z, 0.026147847813081743);
+    s = __builtin_fma(s, z, -0.1907518241219414);
+    s = __builtin_fma(s, z, 0.8117424252833519);
+    s = __builtin_fma(s, z, -1.6449340668482264);
+    return __builtin_fma(r * z, s, r);
 }
 
 __device__ inline void sin_cos(double x, double& sn, double& cs)
@@ -142,8 +131,9 @@ __device__ inline void sin_cos(double x, double& sn, double& cs)
     cs = flip_sign(c, parity);
 }
 
-// Whether every argument of sin_pi / sin_cos on the path stays below kReach.
-// A stage point lies within 2 |T| vmax of x0.  (False for NaN.)
+// Whether every argument (and the double gyre's f and y together) stays below
+// kReach on a path of duration T from p: a stage point lies within 2 |T| vmax of
+// p.  (False for NaN.)
 template <int KIND>
 __device__ inline bool bounded_path(const FlowParams& pr, const double* p, double T)
 {
@@ -152,26 +142,26 @@ __device__ inline bool bounded_path(const FlowParams& pr, const double* p, doubl
         const double va = 2.0 * fabs(T) * kPi * fabs(pr.a), e = fabs(pr.b);
         const double X = fabs(p[0]) + va;
         const double slope = 2.0 * e * X + 1.0 + 2.0 * e;   // >= |df/dx|, and slope * X >= |f|
-        return X < kReach && slope * X < kReach && fabs(p[1]) + va * slope < kReach;
+        return X < kReach && slope * X + fabs(p[1]) + va * slope < kReach;
     } else {
         const double v = 2.0 * fabs(T) * (fabs(pr.a) + fabs(pr.b) + fabs(pr.c));
         return fabs(p[0]) + v < kReach && fabs(p[1]) + v < kReach && fabs(p[2]) + v < kReach;
     }
 }
 
-// The double gyre's velocity at p over (-pi A / 2, pi A / 2), with
-// a = eps sin(omega t) at the stage's time.  (No contraction beyond the written
-// FMAs: on a wall the two sines are the same number and have to cancel.)
+// The double gyre's velocity at p over (-pi^3 A, pi^3 A), with
+// a = eps sin(omega t) at the stage's time.
 __device__ inline void gyre_stage(const double* p, double a, double* v)
 {
 #pragma clang fp contract(off)
     const double g = __builtin_fma(a, p[0], __builtin_fma(a, -2.0, 1.0));   // f = g x, df/dx = g + a x
+    const double kf = rint(g * p[0]), rf = __builtin_fma(g, p[0], -kf);
     const double ky = rint(p[1]), ry = p[1] - ky;
-    const uint32_t parity = (uint32_t)(int)ky;
-    const double sp = sin_pi(__builtin_fma(g, p[0], ry), parity);
-    const double sm = sin_pi(__builtin_fma(g, p[0], -ry), parity);
-    v[0] = sp + sm;
-    v[1] = (sp - sm) * __builtin_fma(a, p[0], g);
+    const uint32_t parity = (uint32_t)(int)(kf + ky);   // the sign of both products
+    const double sf = half_sine(flip_sign(rf, parity)), cf = half_sine(0.5 - fabs(rf));
+    const double sy = half_sine(flip_sign(ry, parity)), cy = half_sine(0.5 - fabs(ry));
+    v[0] = sf * cy;
+    v[1] = cf * sy * __builtin_fma(a, p[0], g);
 }
 
 // The four stages of a double-gyre step take its time factor sin(omega t) at
@@ -186,12 +176,12 @@ constexpr int kAnchor = 32;
 template <int KIND>
 __device__ inline void bounded_steps(const FlowParams& pr, double* p, double ti, double h, int64_t ns)
 {
-    constexpr double kPi = 3.14159265358979323846;
     if constexpr (KIND == 0) {
+        constexpr double kPi3 = 31.00627668029982;   // pi^3 (to 1.4e-17 of it)
         double rsh, rch, rsf, rcf;
         sincos(pr.c * (0.5 * h), &rsh, &rch);
         sincos(pr.c * h, &rsf, &rcf);
-        const double full[2] = {-0.5 * kPi * pr.a * h, 0.5 * kPi * pr.a * h};
+        const double full[2] = {-kPi3 * (pr.a * h), kPi3 * (pr.a * h)};
         const double half[2] = {0.5 * full[0], 0.5 * full[1]};
         const double sixth[2] = {full[0] / 6.0, full[1] / 6.0};
         for (int64_t s0 = 0; s0 < ns; s0 += kAnchor) {

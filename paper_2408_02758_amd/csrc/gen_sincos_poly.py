@@ -6,7 +6,7 @@ precision, is written in Chebyshev polynomials shifted to [0, zmax], cut after
 n terms and written back in powers of z.  The printed bound is the sum of the
 dropped Chebyshev coefficients' magnitudes.
 
-  sin(pi r) = r P(r^2),  |r| <= 1/2     (9 terms)
+  sin(pi r) / pi = r + r^3 P(r^2),  |r| <= 1/2     (8 terms)
   sin(r)    = r P(r^2),  |r| <= pi/2    (9 terms)
   cos(r)    = P(r^2),    |r| <= pi/2    (9 terms)
 """
@@ -50,7 +50,8 @@ def economise(taylor, zmax, n):
 def main():
     half_pi2 = (PI / 2) ** 2
     for name, taylor, zmax, n in (
-            ("sin(pi r) / r", [(-1) ** k * PI ** (2 * k + 1) / factorial(2 * k + 1) for k in range(TERMS)], Fr(1, 4), 9),
+            ("(sin(pi r) / (pi r) - 1) / r^2",
+             [(-1) ** (k + 1) * PI ** (2 * k + 2) / factorial(2 * k + 3) for k in range(TERMS)], Fr(1, 4), 8),
             ("sin(r) / r", [Fr((-1) ** k, factorial(2 * k + 1)) for k in range(TERMS)], half_pi2, 9),
             ("cos(r)", [Fr((-1) ** k, factorial(2 * k)) for k in range(TERMS)], half_pi2, 9)):
         c, bound = economise(taylor, zmax, n)

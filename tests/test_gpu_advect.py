@@ -149,6 +149,28 @@ def test_advect_walls_are_kept():
     assert np.array_equal(got[150:, 0], x[150:, 0])
 
 
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("dist", [1e-6, 1e-9, 1e-12, 1e-200])
+def test_advect_next_to_walls(axis, dist):
+    """A double-gyre particle next to the wall x = 0 or y = 0 keeps its distance to
+    it to a relative tolerance: the normal velocity is the distance times a
+    factor of the other coordinate, in which no absolute error may stand.
+
+    Tolerance: 250 steps round the distance by 2^-53 of it on each side, and
+    their velocities (16 roundings, times h v / y <= 0.04) by less; the other
+    coordinate's error (at most 2 units of 2^-52 a step on each side, stretched
+    by less than exp(5)) moves the factor's integral over T = 5 by less than 15
+    of it: 250 * 4 * 2^-52 * 150 * 15 + 250 * 3 * 2^-53 < 6e-10, within 1e-9."""
+    r = np.random.default_rng(11)
+    x = np.stack([r.random(300) * 2, r.random(300)], 1)
+    x[:, axis] = dist * (1 + r.random(300))
+    ref = oracle.advect_rk4("double_gyre", x, 0.1, 5.0, 0.02)
+    got = F.advect_rk4("double_gyre", torch.as_tensor(x, device=DEV), 0.1, 5.0, 0.02).cpu().numpy()
+    err = np.abs(got[:, axis] / ref[:, axis] - 1.0).max()
+    print(f"[advect next to a wall, axis {axis}, {dist:g}] max rel |d| = {err:.3e}", flush=True)
+    assert err < 1e-9
+
+
 def _gyre_grid(nx, ny, times):
     """The double gyre at the nodes of an nx x ny grid over [0, 2] x [0, 1]."""
     return flows.sampled_field(flows.double_gyre_velocity, [0.0, 0.0], [2.0 / (nx - 1), 1.0 / (ny - 1)], (nx, ny),
