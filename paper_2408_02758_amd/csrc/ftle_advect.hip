@@ -72,9 +72,9 @@ __device__ inline void flow_velocity(const FlowParams& pr, const double* p, doub
 //    particle next to a wall leaves it as it should and one on a wall (y an
 //    integer, x = 0) has a normal velocity of exactly zero.  (Two sines of
 //    f + y and f - y would do, but their sum and difference cancel there.);
-//  - the ABC flow's six values come from three reductions to half a period
-//    (argument - k pi, pi in two parts), one sine and one cosine polynomial each
-//    with the sign (-1)^k, no octant selects;
+//  - the ABC flow's six values come from three reductions to a quarter of a
+//    period, with the reduced argument's rounding carried along, so that its
+//    sines and cosines are as exact as the library's (rms error 2.8e-17);
 //  - the scale factors of the velocity are folded into the steps' h and h/6.
 // The polynomials are Chebyshev economisations of the Taylor series
 // (gen_sincos_poly.py; dropped terms below 4e-18).
@@ -84,7 +84,7 @@ constexpr double kReach = 1073741824.0;   // 2^30: periods fit the 32-bit parity
 // v, negated when the parity's lowest bit is set
 __device__ inline double flip_sign(double v, uint32_t parity)
 {
-    return __longlong_as_double(__double_as_longlong(v) ^ (long long)((unsigned long long)(parity << 31) << 32));
+    return __hiloint2double((int)((uint32_t)__double2hiint(v) ^ (parity << 31 & 0x80000000u)), __double2loint(v));
 }
 
 // sin(pi r) / pi, |r| <= 1/2
@@ -102,33 +102,35 @@ __device__ inline double half_sine(double r)
     return __builtin_fma(r * z, s, r);
 }
 
+// sin x and cos x: r = x - k pi / 2 with its rounding t (the first product's
+// difference is exact), sine and cosine polynomials on |r| <= pi / 4 whose last
+// sum alone rounds, swapped and signed by k's quadrant.
 __device__ inline void sin_cos(double x, double& sn, double& cs)
 {
-    const double k = rint(x * 0.3183098861837907);
-    double r = __builtin_fma(k, -3.141592653589793, x);
-    r = __builtin_fma(k, -1.2246467991473532e-16, r);
+#pragma clang fp contract(off)
+    const double k = rint(x * 0.6366197723675814);
+    const double r1 = __builtin_fma(k, -1.5707963267948966, x);
+    const double r = __builtin_fma(k, -6.123233995736766e-17, r1);
+    const double t = __builtin_fma(k, -6.123233995736766e-17, r1 - r);
     const double z = r * r;
-    const uint32_t parity = (uint32_t)(int)k;
-    double s = 2.7215821926997076e-15;
-    s = __builtin_fma(s, z, -7.643027273612204e-13);
-    s = __builtin_fma(s, z, 1.6058940907182887e-10);
-    s = __builtin_fma(s, z, -2.5052106891168703e-08);
-    s = __builtin_fma(s, z, 2.755731921123654e-06);
-    s = __builtin_fma(s, z, -0.0001984126984120872);
-    s = __builtin_fma(s, z, 0.008333333333333186);
+    double s = 1.5918135932869774e-10;
+    s = __builtin_fma(s, z, -2.5051131947374594e-08);
+    s = __builtin_fma(s, z, 2.7557316103105014e-06);
+    s = __builtin_fma(s, z, -0.0001984126983675979);
+    s = __builtin_fma(s, z, 0.00833333333333095);
     s = __builtin_fma(s, z, -0.16666666666666666);
-    double c = 4.608992189914223e-14;
-    c = __builtin_fma(c, z, -1.1462903400770852e-11);
-    c = __builtin_fma(c, z, 2.087656190004232e-09);
-    c = __builtin_fma(c, z, -2.755731639228085e-07);
-    c = __builtin_fma(c, z, 2.4801587277429444e-05);
-    c = __builtin_fma(c, z, -0.0013888888888773081);
-    c = __builtin_fma(c, z, 0.04166666666666388);
-    c = __builtin_fma(c, z, -0.4999999999999997);
-    c = __builtin_fma(c, z, 1.0);
-    const double rs = flip_sign(r, parity);
-    sn = __builtin_fma(rs * z, s, rs);
-    cs = flip_sign(c, parity);
+    s = r + __builtin_fma(r * z, s, t);
+    double c = -1.1382636115964061e-11;
+    c = __builtin_fma(c, z, 2.087614632531677e-09);
+    c = __builtin_fma(c, z, -2.7557317272036996e-07);
+    c = __builtin_fma(c, z, 2.4801587298766363e-05);
+    c = __builtin_fma(c, z, -0.0013888888888887398);
+    c = __builtin_fma(c, z, 0.041666666666666664);
+    const double w = __builtin_fma(-0.5, z, 1.0);
+    c = w + __builtin_fma(z * z, c, __builtin_fma(-r, t, __builtin_fma(-0.5, z, 1.0 - w)));
+    const uint32_t q = (uint32_t)(int)k;
+    sn = flip_sign(q & 1 ? c : s, q >> 1);
+    cs = flip_sign(q & 1 ? -s : c, q >> 1);
 }
 
 // Whether every argument (and the double gyre's f and y together) stays below

@@ -7,8 +7,8 @@ n terms and written back in powers of z.  The printed bound is the sum of the
 dropped Chebyshev coefficients' magnitudes.
 
   sin(pi r) / pi = r + r^3 P(r^2),  |r| <= 1/2     (8 terms)
-  sin(r)    = r P(r^2),  |r| <= pi/2    (9 terms)
-  cos(r)    = P(r^2),    |r| <= pi/2    (9 terms)
+  sin(r) = r + r^3 P(r^2),  |r| <= pi/4              (6 terms)
+  cos(r) = 1 - r^2/2 + r^4 P(r^2),  |r| <= pi/4      (6 terms)
 """
 from fractions import Fraction as Fr
 from math import factorial
@@ -48,12 +48,12 @@ def economise(taylor, zmax, n):
 
 
 def main():
-    half_pi2 = (PI / 2) ** 2
+    eighth2 = (PI / 4) ** 2
     for name, taylor, zmax, n in (
             ("(sin(pi r) / (pi r) - 1) / r^2",
              [(-1) ** (k + 1) * PI ** (2 * k + 2) / factorial(2 * k + 3) for k in range(TERMS)], Fr(1, 4), 8),
-            ("sin(r) / r", [Fr((-1) ** k, factorial(2 * k + 1)) for k in range(TERMS)], half_pi2, 9),
-            ("cos(r)", [Fr((-1) ** k, factorial(2 * k)) for k in range(TERMS)], half_pi2, 9)):
+            ("(sin(r) / r - 1) / r^2", [Fr((-1) ** (k + 1), factorial(2 * k + 3)) for k in range(TERMS)], eighth2, 6),
+            ("(cos(r) - 1 + r^2/2) / r^4", [Fr((-1) ** k, factorial(2 * k + 4)) for k in range(TERMS)], eighth2, 6)):
         c, bound = economise(taylor, zmax, n)
         print(f"{name}: dropped terms <= {float(bound):.1e}")
         for k, v in enumerate(c):

@@ -171,6 +171,27 @@ def test_advect_next_to_walls(axis, dist):
     assert err < 1e-9
 
 
+def test_advect_sines_keep_their_zeros():
+    """The ABC flow with A = B = 0 moves a particle at x = z = 0 by T C (cos y, 0, sin y):
+    one step shows the sine and cosine of y, which stay relatively exact up to their
+    zeros.
+
+    Tolerance: 2 units of 2^-53 for a function, one for each of the five sums and
+    products of the step, one for the reference: 8 * 2^-53 = 2^-50 of the value."""
+    r = np.random.default_rng(12)
+    near = np.arange(1, 20) * np.pi / 2
+    y = np.concatenate([r.uniform(-30, 30, 20000), near * (1 + 2.0 ** -30), near * (1 - 2.0 ** -25), -near * (1 + 1e-12),
+                        [0.0, np.pi / 2, -np.pi / 2, 1e-300]])
+    x = np.zeros((len(y), 3))
+    x[:, 1] = y
+    got = F.advect_rk4("abc", torch.as_tensor(x, device=DEV), 0.0, 1.0, 1.0, params=(0.0, 0.0, 1.0)).cpu().numpy()
+    assert np.array_equal(got[:, 1], y)
+    for d, ref in ((0, np.cos(y.astype(np.longdouble))), (2, np.sin(y.astype(np.longdouble)))):
+        err = np.abs(got[:, d] - ref)
+        print(f"[advect sines, axis {d}] max rel |d| = {np.max(err[ref != 0] / np.abs(ref[ref != 0])):.3e}", flush=True)
+        assert np.all(err <= 2.0 ** -50 * np.abs(ref))
+
+
 def _gyre_grid(nx, ny, times):
     """The double gyre at the nodes of an nx x ny grid over [0, 2] x [0, 1]."""
     return flows.sampled_field(flows.double_gyre_velocity, [0.0, 0.0], [2.0 / (nx - 1), 1.0 / (ny - 1)], (nx, ny),
