@@ -29,15 +29,15 @@ struct FlowParams {
     double a, b, c;
 };
 
-// Velocity at p, with w the double gyre's time factor sin(omega t) at the
-// stage's time (the steady ABC flow ignores it).
+// Velocity at p by the math library's sines and cosines, with a the double
+// gyre's eps sin(omega t) at the stage's time (the steady ABC flow ignores it).
 template <int KIND>
-__device__ inline void flow_velocity(const FlowParams& pr, const double* p, double w, double* v)
+__device__ inline void flow_velocity(const FlowParams& pr, const double* p, double a, double* v)
 {
     constexpr double kPi = 3.14159265358979323846;
     if constexpr (KIND == 0) {
         double cy, sy, sf, cf;
-        const double a = pr.b * w, b = 1.0 - 2.0 * pr.b * w;
+        const double b = 1.0 - 2.0 * a;
         const double f = (a * p[0] + b) * p[0];
         const double dfdx = 2.0 * a * p[0] + b;
         sincospi(p[1], &sy, &cy);
@@ -56,10 +56,10 @@ __device__ inline void flow_velocity(const FlowParams& pr, const double* p, doub
 }
 
 // ---------------------------------------------------------------------------
-// The bounded path.  Steps in which every argument stays below kReach (known
-// from the position, the time left and the largest velocity) take the sines and
-// cosines written out below; the others (huge or non-finite coordinates and
-// parameters) take flow_velocity's.
+// The bounded path.  Blocks of steps on which every argument stays below kReach
+// (known from the position, their duration and the largest velocity) take the
+// sines and cosines written out below; the others (huge or non-finite
+// coordinates and parameters) take flow_velocity's.
 //
 // A step is float64 instruction issue and nothing else, so the work per stage
 // decides.  The library's sincospi and sincos reduce to an eighth of a period
@@ -77,7 +77,19 @@ __device__ inline void flow_velocity(const FlowParams& pr, const double* p, doub
 //    sines and cosines are as exact as the library's (rms error 2.8e-17);
 //  - the scale factors of the velocity are folded into the steps' h and h/6.
 // The polynomials are Chebyshev economisations of the Taylor series
-// (gen_sincos_poly.py; dropped terms below 4e-18).
+// (gen_sincos_poly.py; dropped terms below 2e-17 of a term that is itself at
+// most 0.6).  Against binary128 a double-gyre velocity's rms error is 4.8e-17
+// (5.5e-17 with the library's functions), 1.3e-16 of it next to a wall (1.6e-16);
+// an ABC velocity's 9.8e-17 (9.7e-17).
+// Vector instructions per step: double gyre 264 (library forms 435), ABC 505
+// (778), all issued back to back (4.2 cycles each).  1024 x 512 particles, 1500
+// double-gyre steps, float32: 5.61 ms (8.87); 81 x 67 x 59 particles, 500 ABC
+// steps, float64: 2.18 ms (3.54).
+//
+// The bound is taken per block: over a whole path it grows with the square of
+// the duration and sent the double gyre to the library's forms from 7e4 time
+// units on (1024 particles, 2e5 steps of 0.5: 245 ms by whole paths, 98 by
+// blocks).
 // ---------------------------------------------------------------------------
 constexpr double kReach = 1073741824.0;   // 2^30: periods fit the 32-bit parity below
 
@@ -166,6 +178,25 @@ __device__ inline void gyre_stage(const double* p, double a, double* v)
     v[1] = cf * sy * __builtin_fma(a, p[0], g);
 }
 
+// The velocity of a stage (BOUNDED double gyre: over its scale, which rk4_steps
+// folds into h), with a = eps sin(omega t) at the stage's time.
+template <int KIND, bool BOUNDED>
+__device__ inline void stage(const FlowParams& pr, const double* p, double a, double* v)
+{
+    if constexpr (!BOUNDED) {
+        flow_velocity<KIND>(pr, p, a, v);
+    } else if constexpr (KIND == 0) {
+        gyre_stage(p, a, v);
+    } else {
+        double s[3], c[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) sin_cos(p[d], s[d], c[d]);
+        v[0] = __builtin_fma(pr.a, s[2], pr.c * c[1]);
+        v[1] = __builtin_fma(pr.b, s[0], pr.a * c[2]);
+        v[2] = __builtin_fma(pr.c, s[1], pr.b * c[0]);
+    }
+}
+
 // The four stages of a double-gyre step take its time factor sin(omega t) at
 // t, t + h/2 (twice) and t + h.  eps (sin, cos)(omega t) advances by a
 // rotation through omega h per step (the half step's value by one through
@@ -175,106 +206,52 @@ __device__ inline void gyre_stage(const double* p, double a, double* v)
 // instructions per value instead of a sine.
 constexpr int kAnchor = 32;
 
-template <int KIND>
-__device__ inline void bounded_steps(const FlowParams& pr, double* p, double ti, double h, int64_t ns)
-{
-    if constexpr (KIND == 0) {
-        constexpr double kPi3 = 31.00627668029982;   // pi^3 (to 1.4e-17 of it)
-        double rsh, rch, rsf, rcf;
-        sincos(pr.c * (0.5 * h), &rsh, &rch);
-        sincos(pr.c * h, &rsf, &rcf);
-        const double full[2] = {-kPi3 * (pr.a * h), kPi3 * (pr.a * h)};
-        const double half[2] = {0.5 * full[0], 0.5 * full[1]};
-        const double sixth[2] = {full[0] / 6.0, full[1] / 6.0};
-        for (int64_t s0 = 0; s0 < ns; s0 += kAnchor) {
-            double a, ac;
-            sincos(pr.c * (ti + (double)s0 * h), &a, &ac);
-            a *= pr.b;
-            ac *= pr.b;
-            const int m = (int)min((int64_t)kAnchor, ns - s0);
-            for (int j = 0; j < m; ++j) {
-                const double ah = __builtin_fma(a, rch, ac * rsh);
-                const double a1 = __builtin_fma(a, rcf, ac * rsf);
-                ac = __builtin_fma(ac, rcf, -(a * rsf));
-                // the stages' sum in velocity units, so that a step rounds the
-                // position once
-                double v[2], q[2], acc[2];
-                gyre_stage(p, a, acc);
-#pragma unroll
-                for (int d = 0; d < 2; ++d) q[d] = __builtin_fma(half[d], acc[d], p[d]);
-                gyre_stage(q, ah, v);
-#pragma unroll
-                for (int d = 0; d < 2; ++d) {
-                    q[d] = __builtin_fma(half[d], v[d], p[d]);
-                    acc[d] = __builtin_fma(2.0, v[d], acc[d]);
-                }
-                gyre_stage(q, ah, v);
-#pragma unroll
-                for (int d = 0; d < 2; ++d) {
-                    q[d] = __builtin_fma(full[d], v[d], p[d]);
-                    acc[d] = __builtin_fma(2.0, v[d], acc[d]);
-                }
-                gyre_stage(q, a1, v);
-#pragma unroll
-                for (int d = 0; d < 2; ++d) p[d] = __builtin_fma(sixth[d], acc[d] + v[d], p[d]);
-                a = a1;
-            }
-        }
-    } else {
-        const double half = 0.5 * h, sixth = h / 6.0;
-        auto stage = [&](const double* x, double* v) {
-            double s[3], c[3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) sin_cos(x[d], s[d], c[d]);
-            v[0] = __builtin_fma(pr.a, s[2], pr.c * c[1]);
-            v[1] = __builtin_fma(pr.b, s[0], pr.a * c[2]);
-            v[2] = __builtin_fma(pr.c, s[1], pr.b * c[0]);
-        };
-        for (int64_t s = 0; s < ns; ++s) {
-            double v[3], q[3], acc[3];
-            stage(p, acc);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) q[d] = __builtin_fma(half, acc[d], p[d]);
-            stage(q, v);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                q[d] = __builtin_fma(half, v[d], p[d]);
-                acc[d] = __builtin_fma(2.0, v[d], acc[d]);
-            }
-            stage(q, v);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                q[d] = __builtin_fma(h, v[d], p[d]);
-                acc[d] = __builtin_fma(2.0, v[d], acc[d]);
-            }
-            stage(q, v);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) p[d] = __builtin_fma(sixth, acc[d] + v[d], p[d]);
-        }
-    }
-}
+struct Rotation {
+    double sh, ch, sf, cf;   // sine and cosine of omega h / 2 and omega h
+};
 
-// Any path, by the math library's sines and cosines.
-template <int KIND>
-__device__ inline void general_steps(const FlowParams& pr, double* p, double ti, double h, int64_t ns)
+// m steps of h from p, with (a, ac) = eps (sin, cos)(omega t) at their start.
+template <int KIND, bool BOUNDED>
+__device__ inline void rk4_steps(const FlowParams& pr, double* p, double a, double ac, const Rotation& rot, double h,
+                                 int m)
 {
     constexpr int D = KIND == 0 ? 2 : 3;
-    double q[D], k1[D], k2[D], k3[D], k4[D];
-    for (int64_t s = 0; s < ns; ++s) {
-        const double t = ti + (double)s * h;
-        flow_velocity<KIND>(pr, p, KIND == 0 ? sin(pr.c * t) : 0.0, k1);
-        const double wh = KIND == 0 ? sin(pr.c * (t + 0.5 * h)) : 0.0;
+    double full[D], half[D], sixth[D];
 #pragma unroll
-        for (int d = 0; d < D; ++d) q[d] = p[d] + 0.5 * h * k1[d];
-        flow_velocity<KIND>(pr, q, wh, k2);
+    for (int d = 0; d < D; ++d) {
+        constexpr double kPi3 = 31.00627668029982;   // pi^3 (to 1.4e-17 of it)
+        full[d] = !BOUNDED || KIND == 1 ? h : (d == 0 ? -kPi3 : kPi3) * (pr.a * h);
+        half[d] = 0.5 * full[d];
+        sixth[d] = full[d] / 6.0;
+    }
+    for (int j = 0; j < m; ++j) {
+        double ah = 0.0, a1 = 0.0;
+        if constexpr (KIND == 0) {
+            ah = __builtin_fma(a, rot.ch, ac * rot.sh);
+            a1 = __builtin_fma(a, rot.cf, ac * rot.sf);
+            ac = __builtin_fma(ac, rot.cf, -(a * rot.sf));
+        }
+        // the stages' sum in velocity units, so that a step rounds the position once
+        double v[D], q[D], acc[D];
+        stage<KIND, BOUNDED>(pr, p, a, acc);
 #pragma unroll
-        for (int d = 0; d < D; ++d) q[d] = p[d] + 0.5 * h * k2[d];
-        flow_velocity<KIND>(pr, q, wh, k3);
+        for (int d = 0; d < D; ++d) q[d] = __builtin_fma(half[d], acc[d], p[d]);
+        stage<KIND, BOUNDED>(pr, q, ah, v);
 #pragma unroll
-        for (int d = 0; d < D; ++d) q[d] = p[d] + h * k3[d];
-        flow_velocity<KIND>(pr, q, KIND == 0 ? sin(pr.c * (t + h)) : 0.0, k4);
+        for (int d = 0; d < D; ++d) {
+            q[d] = __builtin_fma(half[d], v[d], p[d]);
+            acc[d] = __builtin_fma(2.0, v[d], acc[d]);
+        }
+        stage<KIND, BOUNDED>(pr, q, ah, v);
 #pragma unroll
-        for (int d = 0; d < D; ++d) p[d] += h / 6.0 * (k1[d] + 2.0 * k2[d] + 2.0 * k3[d] + k4[d]);
+        for (int d = 0; d < D; ++d) {
+            q[d] = __builtin_fma(full[d], v[d], p[d]);
+            acc[d] = __builtin_fma(2.0, v[d], acc[d]);
+        }
+        stage<KIND, BOUNDED>(pr, q, a1, v);
+#pragma unroll
+        for (int d = 0; d < D; ++d) p[d] = __builtin_fma(sixth[d], acc[d] + v[d], p[d]);
+        a = a1;
     }
 }
 
@@ -299,10 +276,24 @@ __global__ void __launch_bounds__(256) advect_kernel(FlowParams pr, int64_t n, c
     }
     const double h = Ti / steps;
     const int64_t ns = (int64_t)steps;
-    if (bounded_path<KIND>(pr, p, Ti))
-        bounded_steps<KIND>(pr, p, ti, h, ns);
-    else
-        general_steps<KIND>(pr, p, ti, h, ns);
+    Rotation rot{};
+    if constexpr (KIND == 0) {
+        sincos(pr.c * (0.5 * h), &rot.sh, &rot.ch);
+        sincos(pr.c * h, &rot.sf, &rot.cf);
+    }
+    for (int64_t s = 0; s < ns; s += kAnchor) {
+        const int m = (int)min((int64_t)kAnchor, ns - s);
+        double a = 0.0, ac = 0.0;
+        if constexpr (KIND == 0) {
+            sincos(pr.c * (ti + (double)s * h), &a, &ac);
+            a *= pr.b;
+            ac *= pr.b;
+        }
+        if (bounded_path<KIND>(pr, p, m * h))
+            rk4_steps<KIND, true>(pr, p, a, ac, rot, h, m);
+        else
+            rk4_steps<KIND, false>(pr, p, a, ac, rot, h, m);
+    }
 #pragma unroll
     for (int d = 0; d < D; ++d) phi[i * D + d] = (T)p[d];
 }

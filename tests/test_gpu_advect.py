@@ -192,6 +192,24 @@ def test_advect_sines_keep_their_zeros():
         assert np.all(err <= 2.0 ** -50 * np.abs(ref))
 
 
+@pytest.mark.parametrize("flow", ["double_gyre", "abc"])
+def test_advect_reach_by_blocks(flow):
+    """The step form is chosen for blocks of 32 steps: particles about the reach, some
+    of them on either side of it in different blocks, over two and a half blocks.
+
+    Tolerance, u = 2^-22 the spacing of positions below 2^30: 80 steps round the
+    position by u / 2 and carry u of phase, on each side, stretched by less than
+    exp(2 * 1.6) < 25: 80 * 3/2 * 2 * 25 u = 6000 u."""
+    x = meshes.jittered_tri_grid(25, 20, seed=3)[0] if flow == "double_gyre" else meshes.kuhn_tet_grid(8)[0]
+    x = x.copy()
+    last = x.shape[1] - 1
+    x[:, last] += 2.0 ** 30 - np.random.default_rng(5).uniform(0.0, 20.0, x.shape[0])
+    t0, T, dt = 0.3, 1.6, 0.02
+    ref = oracle.advect_rk4(flow, x, t0, T, dt)
+    got = F.advect_rk4(flow, torch.as_tensor(x, device=DEV), t0, T, dt).cpu().numpy()
+    assert np.abs(got - ref).max() <= 6000 * 2.0 ** -22
+
+
 def _gyre_grid(nx, ny, times):
     """The double gyre at the nodes of an nx x ny grid over [0, 2] x [0, 1]."""
     return flows.sampled_field(flows.double_gyre_velocity, [0.0, 0.0], [2.0 / (nx - 1), 1.0 / (ny - 1)], (nx, ny),
