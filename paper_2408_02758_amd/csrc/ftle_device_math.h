@@ -92,25 +92,27 @@ __device__ inline void cubic_qpr(T c00, T c01, T c02, T c11, T c12, T c22, T& q,
 }
 
 // double: c = cos((2/3) acos(s)), s = sqrt((1 + r)/2), as a polynomial in
-// u = s - 1/2 on [0, 1] (csrc/gen_eig_poly.py; dropped terms 3.7e-18, error in
-// Horner form 1.1e-16): half the instructions of the library's acos and cos.
+// u = s - kEigCentre on s in [0, 1] (csrc/gen_eig_poly.py; dropped terms 3.7e-18,
+// rms error 3.5e-17 in Horner form, 4.4e-17 by the library's acos and cos): half
+// the library's instructions.
 // Its coefficients are read (scalar loads) where they are used, through a
 // pointer the compiler cannot see behind: as literals it keeps them in vector
 // registers across the loop over a tile's rows, and the 3D float64 forward
 // then no longer fits the 128 registers of four waves per SIMD.
+constexpr double kEigCentre = 0.495758056640625;
 __constant__ double kEigPoly[20] = {
-    0.766044443118978, 0.49481813264570607, -0.062036753745945694, 0.019730822520698705,
-    -0.008065995058000701, 0.003725614493912388, -0.001850875932177013, 0.0009652580660097717,
-    -0.0005211824563454097, 0.00028884529336952754, -0.00016337446432180538, 9.392215760218694e-05,
-    -5.466191327612715e-05, 3.219016325584648e-05, -1.9464458091489548e-05, 1.1714871704272548e-05,
-    -5.982240282331103e-06, 3.543752785969229e-06, -4.217695979632236e-06, 2.664713851949588e-06};
+    0.7639443348239103, 0.4953455130198401, -0.062288718534549974, 0.019868357724094367,
+    -0.008145516449145062, 0.0037730893463692656, -0.0018798023752576013, 0.0009831332944527135,
+    -0.0005323433262451434, 0.00029586942340298036, -0.00016782262760955773, 9.675035663212685e-05,
+    -5.646933103360268e-05, 3.3368495378284505e-05, -2.0222970974162425e-05, 1.2129831194836975e-05,
+    -6.249599867215179e-06, 3.873994173388842e-06, -4.432463718981566e-06, 2.664713851949588e-06};
 
 __device__ inline double lam_max3_poly(double c00, double c01, double c02, double c11, double c12, double c22,
                                        double& r)
 {
     double q, p;
     cubic_qpr<double>(c00, c01, c02, c11, c12, c22, q, p, r);
-    const double u = sqrt(0.5 * (1.0 + r)) - 0.5;
+    const double u = sqrt(0.5 * (1.0 + r)) - kEigCentre;
     const __attribute__((address_space(4))) double* k = (const __attribute__((address_space(4))) double*)kEigPoly;
     asm volatile("" : "+s"(k));
     double c = k[19];

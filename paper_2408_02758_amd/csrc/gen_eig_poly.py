@@ -9,14 +9,18 @@ c(1) = 1).  This script fits it by least squares in the Chebyshev basis on
 Horner evaluation in float32 (max error about 1.2e-7 in c).
 
 For float64 (coefficients64) the polynomial is the Chebyshev economisation of
-c's Taylor series about s = 1/2, in powers of u = s - 1/2 (whose coefficients
-shrink, unlike those of powers of s), in rational arithmetic: c satisfies
+c's Taylor series about s = 1/2, in powers of u = s - S0 (whose coefficients
+shrink, unlike those of powers of s), in rational arithmetic.  S0 lies next to
+1/2 where the first two coefficients happen to be doubles to 1/100 of a rounding
+(at 1/2 theirs biased c by 2.8e-17).  c satisfies
 (1 - s^2) c'' - s c' + (4/9) c = 0, which gives the series from c(1/2) =
 cos 40 deg (a root of 8 x^3 - 6 x + 1) and c'(1/2) = (2/3) sin 40 deg / sin 60 deg.
 """
 from fractions import Fraction as Fr
 
 import numpy as np
+
+S0 = Fr(32768 - 278, 65536)
 
 
 def coefficients(deg: int = 7):
@@ -38,7 +42,7 @@ def _newton(f, df, x):
 
 
 def coefficients64(n: int = 20, terms: int = 60):
-    """(coefficients of u^0 .. u^(n-1), sum of the dropped Chebyshev coefficients)."""
+    """(coefficients of (s - S0)^0 .. (s - S0)^(n-1), sum of the dropped Chebyshev coefficients)."""
     c0 = _newton(lambda x: 8 * x ** 3 - 6 * x + 1, lambda x: 24 * x * x - 6, Fr(766, 1000))
     s0 = _newton(lambda x: x * x - (1 - c0 * c0), lambda x: 2 * x, Fr(643, 1000))
     sin60 = _newton(lambda x: x * x - Fr(3, 4), lambda x: 2 * x, Fr(866, 1000))
@@ -61,12 +65,16 @@ def coefficients64(n: int = 20, terms: int = 60):
     for k in range(n):
         for i, v in enumerate(t[k]):
             out[i] += cheb[k] * v
-    return [float(v * 2 ** k) for k, v in enumerate(out)], float(sum(abs(v) for v in cheb[n:]))
+    out = [v * 2 ** k for k, v in enumerate(out)]
+    for i in range(n):                             # powers of s - 1/2 to powers of s - S0
+        for k in range(n - 2, i - 1, -1):
+            out[k] += (S0 - Fr(1, 2)) * out[k + 1]
+    return [float(v) for v in out], float(sum(abs(v) for v in cheb[n:]))
 
 
 if __name__ == "__main__":
     coef, err = coefficients64()
-    print(f"// float64, powers of s - 1/2; dropped terms {err:.1e}")
+    print(f"// float64, powers of s - {float(S0)!r}; dropped terms {err:.1e}")
     for k, a in enumerate(coef):
         print(f"// u^{k}: {a!r}")
     coef, err = coefficients()
