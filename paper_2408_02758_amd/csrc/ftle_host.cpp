@@ -28,6 +28,7 @@
 
 #include "../../include/ftle.h"
 #include "ftle_internal.h"
+#include "ftle_memory.h"
 
 using namespace ftle;
 
@@ -656,121 +657,16 @@ TileSet build_tiles(int dim, bool f64, int64_t n, const std::vector<Chunk>& chun
 // ---------------------------------------------------------------------------
 // Device memory
 // ---------------------------------------------------------------------------
-// The memory of destroyed meshes (and of a build's own temporaries) is kept
-// for the next ones, per device, up to kPoolBound bytes: a program that rebuilds
-// its mesh in every frame otherwise pays for mapping and unmapping it each time
-// (127 x 113 x 101 points: 0.8 ms to free a mesh, 0.3 to allocate one, of 3.2 ms
-// a frame).  A block is given back only when no kernel can still use it
-// (release_device waits for the device, a build for its stream) and taken again
-// for a request of the same size class (an eighth of a power of two).  Beyond
-// the bound the blocks given back first are freed; ftle_release_cached_memory
-// frees all of them, and so does an allocation that would fail otherwise.
-constexpr int kMaxCachedDevices = 64;
-constexpr size_t kPoolBound = size_t(1) << 30;
-
-struct DevPool {
-    std::mutex m;
-    std::vector<std::pair<size_t, void*>> idle;   // (class size, block), oldest first
-    size_t idle_bytes = 0;
-    std::map<void*, size_t> live;                 // blocks in use and their class sizes
-};
-
-// Never destroyed: a mesh may outlive static destructors, and the end of the
-// process returns the memory anyway.
-DevPool* pools()
+void* dev_alloc(size_t bytes)
 {
-    static DevPool* const all = new DevPool[kMaxCachedDevices];
-    return all;
-}
-
-DevPool* device_pool()   // the current device's
-{
-    int dev = -1;
-    check_hip(hipGetDevice(&dev), "hipGetDevice (no usable GPU?)");
-    return dev >= 0 && dev < kMaxCachedDevices ? pools() + dev : nullptr;
-}
-
-size_t pool_class(size_t bytes)
-{
-    size_t step = 64;
-    while (step * 16 <= bytes) step *= 2;   // 8 to 16 steps: the sizes of one power of two, in eighths
-    return (std::max<size_t>(bytes, 1) + step - 1) / step * step;
-}
-
-// Frees idle blocks of the current device, oldest first, until `keep` bytes are left.
-void pool_trim(DevPool* pool, size_t keep)
-{
-    std::vector<void*> drop;
-    {
-        std::lock_guard<std::mutex> lk(pool->m);
-        size_t k = 0;
-        for (; k < pool->idle.size() && pool->idle_bytes > keep; ++k) {
-            pool->idle_bytes -= pool->idle[k].first;
-            drop.push_back(pool->idle[k].second);
-        }
-        pool->idle.erase(pool->idle.begin(), pool->idle.begin() + (std::ptrdiff_t)k);
-    }
-    for (void* p : drop) (void)hipFree(p);
-}
-
-void* pool_alloc(size_t bytes)
-{
-    DevPool* pool = device_pool();
-    const size_t size = pool_class(bytes);
     void* p = nullptr;
-    if (pool) {
-        std::lock_guard<std::mutex> lk(pool->m);
-        for (size_t k = pool->idle.size(); k-- > 0;)
-            if (pool->idle[k].first == size) {
-                p = pool->idle[k].second;
-                pool->idle.erase(pool->idle.begin() + (std::ptrdiff_t)k);
-                pool->idle_bytes -= size;
-                pool->live[p] = size;
-                return p;
-            }
-    }
-    hipError_t e = hipMalloc(&p, size);
-    if (e == hipErrorOutOfMemory && pool) {
-        (void)hipGetLastError();
-        pool_trim(pool, 0);
-        e = hipMalloc(&p, size);
-    }
-    check_hip(e, "hipMalloc");
-    if (pool) {
-        std::lock_guard<std::mutex> lk(pool->m);
-        pool->live[p] = size;
-    }
+    check_hip(pool_alloc(&p, bytes), "device memory");
     return p;
-}
-
-// Gives a block of the current device back; no kernel may still use it.
-void pool_free(void* p) noexcept
-{
-    if (!p) return;
-    try {
-        DevPool* pool = device_pool();
-        if (pool) {
-            {
-                std::lock_guard<std::mutex> lk(pool->m);
-                auto it = pool->live.find(p);
-                if (it != pool->live.end()) {
-                    const size_t size = it->second;
-                    pool->live.erase(it);
-                    pool->idle.push_back({size, p});
-                    pool->idle_bytes += size;
-                    p = nullptr;
-                }
-            }
-            pool_trim(pool, kPoolBound);
-        }
-    } catch (...) {
-    }
-    if (p) (void)hipFree(p);
 }
 
 void* dev_upload(const void* src, size_t bytes)
 {
-    void* p = pool_alloc(bytes);
+    void* p = dev_alloc(bytes);
     if (src && bytes) {
         const hipError_t e = hipMemcpy(p, src, bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
@@ -1256,7 +1152,7 @@ std::vector<double> checked_coords(int dim, int64_t n_points, const void* coords
 struct DevBuf {
     void* p = nullptr;
     DevBuf() = default;
-    explicit DevBuf(size_t bytes) : p(pool_alloc(bytes)) {}
+    explicit DevBuf(size_t bytes) : p(dev_alloc(bytes)) {}
     ~DevBuf() { reset(); }
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
@@ -1286,62 +1182,20 @@ struct DevBuf {
 
 // The build's temporaries, carved from one allocation: a hipMalloc / hipFree
 // pair per temporary array cost more than the kernels that use them.
-// Scratch device memory of the device mesh builds, kept per device between
-// builds and grown when a build needs more, so that a build does not pay for
-// allocating and releasing its temporaries each time.  One build at a time
-// holds it (a concurrent build on the same device takes memory of its own);
-// ftle_release_cached_memory frees it.  Never freed by a static destructor:
-// the runtime may be gone by then, and the process's end returns it anyway.
-struct BuildScratch {
-    std::mutex m;
-    void* p = nullptr;
-    size_t bytes = 0;
-    bool busy = false;
-};
-BuildScratch g_build_scratch[kMaxCachedDevices];
-
 class ScratchLease {
   public:
     ScratchLease(size_t need, hipStream_t s) : s_(s)
     {
-        int dev = -1;
-        check_hip(hipGetDevice(&dev), "hipGetDevice");
-        if (dev >= 0 && dev < kMaxCachedDevices) {
-            BuildScratch& c = g_build_scratch[dev];
-            std::lock_guard<std::mutex> lk(c.m);
-            if (!c.busy) {
-                if (c.bytes < need) {
-                    if (c.p) (void)hipFree(c.p);
-                    c.p = nullptr;
-                    c.bytes = 0;
-                    check_hip(hipMalloc(&c.p, need ? need : 16), "hipMalloc (mesh build scratch)");
-                    c.bytes = need;
-                }
-                c.busy = true;
-                cache_ = &c;
-                p_ = c.p;
-                return;
-            }
-        }
-        own_ = DevBuf(need);
-        p_ = own_.p;
+        check_hip(scratch_take(need, &hold_), "device memory (mesh build scratch)");
     }
-    ~ScratchLease()
-    {
-        (void)hipStreamSynchronize(s_);   // the build's kernels are done with it (also after a failure)
-        if (!cache_) return;
-        std::lock_guard<std::mutex> lk(cache_->m);
-        cache_->busy = false;
-    }
+    ~ScratchLease() { scratch_return(hold_, s_); }
     ScratchLease(const ScratchLease&) = delete;
     ScratchLease& operator=(const ScratchLease&) = delete;
-    void* get() const { return p_; }
+    void* get() const { return hold_.p; }
 
   private:
     hipStream_t s_;
-    BuildScratch* cache_ = nullptr;
-    DevBuf own_;
-    void* p_ = nullptr;
+    ScratchHold hold_;
 };
 
 struct Arena {
@@ -2132,7 +1986,7 @@ ftle_status ftle_backward(ftle_mesh_t mesh, const void* flow, ftle_dtype dtype, 
         hipStream_t s = static_cast<hipStream_t>(stream);
         if (!mesh->d_work) {
             const size_t bytes = (size_t)mesh->n * (2 * mesh->dim + 1) * mesh->elem();
-            mesh->d_work = pool_alloc(bytes);
+            mesh->d_work = dev_alloc(bytes);
         } else if (mesh->work_stream != s) {
             // the previous call on another stream may still use the workspace
             check_hip(hipStreamWaitEvent(s, mesh->work_done, 0), "hipStreamWaitEvent");
@@ -2435,24 +2289,15 @@ ftle_status ftle_release_cached_memory(void)
     return guarded([&] {
         int cur = -1;   // the current device, read once something is to be freed
         for (int dev = 0; dev < kMaxCachedDevices; ++dev) {
-            BuildScratch& c = g_build_scratch[dev];
-            std::lock_guard<std::mutex> lk(c.m);
-            DevPool* pool = pools() + dev;
-            bool pooled = false;
+            Kept& k = *kept(dev);
             {
-                std::lock_guard<std::mutex> lp(pool->m);
-                pooled = !pool->idle.empty();
+                std::lock_guard<std::mutex> lk(k.scratch.m);
+                std::lock_guard<std::mutex> lp(k.pool.m);
+                if (k.pool.idle.empty() && (!k.scratch.p || k.scratch.busy)) continue;
             }
-            const bool scratch = c.p && !c.busy;
-            if (!pooled && !scratch) continue;
             if (cur < 0) check_hip(hipGetDevice(&cur), "hipGetDevice");
             check_hip(hipSetDevice(dev), "hipSetDevice");
-            if (pooled) pool_trim(pool, 0);
-            if (scratch) {
-                (void)hipFree(c.p);
-                c.p = nullptr;
-                c.bytes = 0;
-            }
+            release_kept(k);
         }
         if (cur >= 0) check_hip(hipSetDevice(cur), "hipSetDevice");
     });
@@ -2464,11 +2309,10 @@ ftle_status ftle_cached_memory_bytes(int64_t* bytes)
         if (!bytes) fail(FTLE_ERR_INVALID_ARG, "bytes is NULL");
         int64_t total = 0;
         for (int dev = 0; dev < kMaxCachedDevices; ++dev) {
-            BuildScratch& c = g_build_scratch[dev];
-            std::lock_guard<std::mutex> lk(c.m);
-            DevPool* pool = pools() + dev;
-            std::lock_guard<std::mutex> lp(pool->m);
-            total += (int64_t)(c.bytes + pool->idle_bytes);
+            Kept& k = *kept(dev);
+            std::lock_guard<std::mutex> lk(k.scratch.m);
+            std::lock_guard<std::mutex> lp(k.pool.m);
+            total += (int64_t)(k.scratch.bytes + k.pool.idle_bytes);
         }
         *bytes = total;
     });

@@ -1,0 +1,93 @@
+// The kept device memory (ftle_memory.h) against a pretend device: the HIP
+// calls below stand in for the runtime's.  Prints the first check that fails.
+#include "ftle_memory.h"
+
+#include <cstdio>
+#include <cstring>
+#include <set>
+
+static std::map<void*, size_t> g_held;   // allocations of the pretend device
+static size_t g_used = 0, g_capacity = size_t(1) << 40;
+static char* g_next = reinterpret_cast<char*>(size_t(1) << 32);
+
+extern "C" {
+hipError_t hipGetDevice(int* dev)
+{
+    *dev = 0;
+    return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t bytes)
+{
+    if (g_used + bytes > g_capacity) return hipErrorOutOfMemory;
+    *p = g_next;
+    g_next += bytes + 4096;
+    g_held[*p] = bytes;
+    g_used += bytes;
+    return hipSuccess;
+}
+hipError_t hipFree(void* p)
+{
+    auto it = g_held.find(p);
+    if (it == g_held.end()) return hipErrorInvalidValue;
+    g_used -= it->second;
+    g_held.erase(it);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+}
+
+using namespace ftle;
+
+#define CHECK(x)                                               \
+    if (!(x)) {                                                \
+        std::printf("%s:%d: %s\n", __FILE__, __LINE__, #x);    \
+        return 1;                                              \
+    }
+
+static const size_t MiB = size_t(1) << 20;
+
+// An allocation finds the memory that the library keeps, whoever keeps it.
+static int out_of_memory()
+{
+    // 600 MiB idle in the pool of a device of 1000: the scratch needs 700
+    g_capacity = 1000 * MiB;
+    void* p = nullptr;
+    CHECK(pool_alloc(&p, 600 * MiB) == hipSuccess);
+    pool_free(p);
+    CHECK(kept(0)->pool.idle_bytes >= 600 * MiB);
+    ScratchHold h;
+    CHECK(scratch_take(700 * MiB, &h) == hipSuccess && h.p && h.cache);
+    CHECK(kept(0)->pool.idle_bytes == 0);
+    // a second build of 200 MiB beside it, then one of 400 that nothing can serve
+    ScratchHold own, none;
+    CHECK(scratch_take(200 * MiB, &own) == hipSuccess && own.p && !own.cache);
+    CHECK(scratch_take(400 * MiB, &none) == hipErrorOutOfMemory && !none.p);
+    scratch_return(own, nullptr);
+    scratch_return(h, nullptr);
+    // the idle scratch of 700 MiB gives way to a mesh of 600, a busy one does not
+    CHECK(pool_alloc(&p, 600 * MiB) == hipSuccess);
+    CHECK(kept(0)->scratch.p == nullptr && kept(0)->scratch.bytes == 0);
+    CHECK(scratch_take(300 * MiB, &h) == hipSuccess && h.cache);
+    void* q = nullptr;
+    CHECK(pool_alloc(&q, 200 * MiB) == hipErrorOutOfMemory);
+    CHECK(kept(0)->scratch.p == h.p);
+    // a scratch that cannot grow is given up whole, and the next build takes it again
+    scratch_return(h, nullptr);
+    CHECK(scratch_take(500 * MiB, &h) == hipErrorOutOfMemory && !h.p);
+    CHECK(!kept(0)->scratch.busy && kept(0)->scratch.bytes == 0);
+    CHECK(scratch_take(300 * MiB, &h) == hipSuccess && h.cache);
+    scratch_return(h, nullptr);
+    pool_free(p);
+    release_kept(*kept(0));
+    CHECK(g_held.empty() && g_used == 0);
+    return 0;
+}
+
+int main(int argc, char** argv)
+{
+    const char* name = argc > 1 ? argv[1] : "";
+    if (!std::strcmp(name, "out_of_memory")) return out_of_memory();
+    std::printf("no check of that name\n");
+    return 2;
+}
