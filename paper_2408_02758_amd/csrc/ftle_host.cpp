@@ -670,18 +670,18 @@ void* dev_upload(const void* src, size_t bytes)
     if (src && bytes) {
         const hipError_t e = hipMemcpy(p, src, bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
-            pool_free(p);
+            pool_free(p, false);
             check_hip(e, "hipMemcpy");
         }
     }
     return p;
 }
 
-void free_tiles(TileSet& t)
+void free_tiles(TileSet& t, const GiveBack& give)
 {
-    pool_free(t.d_meta);
-    pool_free(t.d_rec);
-    pool_free(t.d_minv);
+    give(t.d_meta);
+    give(t.d_rec);
+    give(t.d_minv);
     t.d_meta = t.d_rec = t.d_minv = nullptr;
 }
 
@@ -697,16 +697,16 @@ void release_device(ftle_mesh_s* m)
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(m->device);
-    (void)hipDeviceSynchronize();
-    free_tiles(m->fwd);
-    free_tiles(m->bwd);
-    pool_free(m->d_x);
-    pool_free(m->d_hits);
-    pool_free(m->d_work);
+    const GiveBack give;
+    free_tiles(m->fwd, give);
+    free_tiles(m->bwd, give);
+    give(m->d_x);
+    give(m->d_hits);
+    give(m->d_work);
     if (m->work_done) (void)hipEventDestroy(m->work_done);
-    pool_free(m->d_perm);
-    pool_free(m->d_row_ptr);
-    pool_free(m->d_col);
+    give(m->d_perm);
+    give(m->d_row_ptr);
+    give(m->d_col);
     m->d_perm = nullptr;
     m->d_row_ptr = nullptr;
     m->d_col = nullptr;
@@ -1168,8 +1168,10 @@ struct DevBuf {
     }
     void reset()
     {
-        if (p && std::uncaught_exceptions() > 0) (void)hipDeviceSynchronize();
-        pool_free(p);
+        if (p && std::uncaught_exceptions() > 0)
+            GiveBack()(p);
+        else
+            pool_free(p);
         p = nullptr;
     }
     void* release()
@@ -2243,21 +2245,21 @@ void apply_pin(BatchPlan* p, const PinnedShape& pin)
     drop_graph(p);
 }
 
-void free_plan(BatchPlan* p)
+void free_plan(BatchPlan* p, const GiveBack& give)
 {
     drop_graph(p);
     if (p->done) (void)hipEventDestroy(p->done);
-    pool_free(p->d_items);
-    pool_free(p->d_queue);
+    give(p->d_items);
+    give(p->d_queue);
 }
 
 // Drop every cached batch plan that references mesh (its device pointers die with it).
-void purge_plans(ftle_mesh_t mesh)
+void purge_plans(ftle_mesh_t mesh, const GiveBack& give)
 {
     std::lock_guard<std::mutex> lk(g_batch_mu);
     for (auto it = g_plans.begin(); it != g_plans.end();) {
         if (std::find(it->first.begin(), it->first.end(), mesh) != it->first.end()) {
-            free_plan(it->second.get());
+            free_plan(it->second.get(), give);
             it = g_plans.erase(it);
         } else {
             ++it;
@@ -2276,8 +2278,7 @@ void ftle_destroy_mesh(ftle_mesh_t mesh)
         int cur = 0;
         (void)hipGetDevice(&cur);
         (void)hipSetDevice(mesh->device);
-        (void)hipDeviceSynchronize();
-        purge_plans(mesh);
+        purge_plans(mesh, GiveBack());
         (void)hipSetDevice(cur);
     }
     release_device(mesh);

@@ -19,9 +19,10 @@ namespace {
 // for the next ones, per device, up to kPoolBound bytes: a program that rebuilds
 // its mesh in every frame otherwise pays for mapping and unmapping it each time
 // (127 x 113 x 101 points: 0.8 ms to free a mesh, 0.3 to allocate one, of 3.2 ms
-// a frame).  A block is given back only when no kernel can still use it
-// (release_device waits for the device, a build for its stream) and taken again
-// for a request of the same size class (an eighth of a power of two).  Beyond
+// a frame).  A block is kept only when no kernel can still use it
+// (release_device waits for the device, a build for its stream; where that wait
+// fails the block goes to hipFree) and taken again for a request of the same size
+// class (an eighth of a power of two).  Beyond
 // the bound the blocks given back first are freed; ftle_release_cached_memory
 // frees all of them, and so does an allocation that would fail otherwise.
 constexpr int kMaxCachedDevices = 64;
@@ -141,8 +142,9 @@ hipError_t pool_alloc(void** p, size_t bytes)
     return hipSuccess;
 }
 
-// Gives a block back; no kernel may still use it.
-void pool_free(void* p) noexcept
+// Gives a block back: kept for reuse if `done`, which says that no kernel can
+// still use it, else freed.
+void pool_free(void* p, bool done = true) noexcept
 {
     if (!p) return;
     try {
@@ -155,9 +157,11 @@ void pool_free(void* p) noexcept
                 if (it != k->pool.live.end()) {
                     const size_t size = it->second;
                     k->pool.live.erase(it);
-                    k->pool.idle.push_back({size, p});
-                    k->pool.idle_bytes += size;
-                    p = nullptr;
+                    if (done) {
+                        k->pool.idle.push_back({size, p});
+                        k->pool.idle_bytes += size;
+                        p = nullptr;
+                    }
                 }
             }
             pool_trim(k->pool, kPoolBound);
@@ -166,6 +170,12 @@ void pool_free(void* p) noexcept
     }
     if (p) (void)hipFree(p);
 }
+
+// Gives blocks back after waiting for everything on the device.
+struct GiveBack {
+    const bool done = hipDeviceSynchronize() == hipSuccess;
+    void operator()(void* p) const noexcept { pool_free(p, done); }
+};
 
 // A build's hold on the scratch, or on memory of its own while another has it.
 struct ScratchHold {
@@ -213,11 +223,16 @@ hipError_t scratch_take(size_t need, ScratchHold* h)
 // The build's kernels on s are waited for (also after a failure).
 void scratch_return(ScratchHold& h, hipStream_t s) noexcept
 {
-    (void)hipStreamSynchronize(s);
+    const bool done = hipStreamSynchronize(s) == hipSuccess;
     if (!h.cache) {
-        pool_free(h.p);
+        pool_free(h.p, done);
     } else {
         std::lock_guard<std::mutex> lk(h.cache->m);
+        if (!done) {
+            (void)hipFree(h.cache->p);
+            h.cache->p = nullptr;
+            h.cache->bytes = 0;
+        }
         h.cache->busy = false;
     }
     h = ScratchHold{};

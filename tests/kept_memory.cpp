@@ -8,6 +8,7 @@
 
 static std::map<void*, size_t> g_held;   // allocations of the pretend device
 static size_t g_used = 0, g_capacity = size_t(1) << 40;
+static hipError_t g_wait = hipSuccess;   // what a wait returns
 static char* g_next = reinterpret_cast<char*>(size_t(1) << 32);
 
 extern "C" {
@@ -34,7 +35,8 @@ hipError_t hipFree(void* p)
     g_held.erase(it);
     return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return g_wait; }
+hipError_t hipDeviceSynchronize() { return g_wait; }
 }
 
 using namespace ftle;
@@ -84,10 +86,38 @@ static int out_of_memory()
     return 0;
 }
 
+// Memory whose kernels could not be waited for is not handed out again.
+static int failed_wait()
+{
+    void *a = nullptr, *b = nullptr;
+    CHECK(pool_alloc(&a, 5 * MiB) == hipSuccess);
+    g_wait = hipErrorStreamCaptureUnsupported;
+    GiveBack()(a);
+    CHECK(!g_held.count(a) && kept(0)->pool.idle.empty() && kept(0)->pool.live.empty());
+    CHECK(pool_alloc(&b, 5 * MiB) == hipSuccess && b != a);
+    // a build's scratch, and the memory of one beside it
+    ScratchHold h, own;
+    CHECK(scratch_take(MiB, &h) == hipSuccess && scratch_take(MiB, &own) == hipSuccess && !own.cache);
+    void *p = h.p, *q = own.p;
+    scratch_return(own, nullptr);
+    scratch_return(h, nullptr);
+    CHECK(!g_held.count(p) && !g_held.count(q) && kept(0)->scratch.bytes == 0 && !kept(0)->scratch.busy);
+    CHECK(scratch_take(MiB, &h) == hipSuccess && h.cache && h.p != p && h.p != q);
+    // with waits that succeed they are kept
+    g_wait = hipSuccess;
+    GiveBack()(b);
+    p = h.p;
+    scratch_return(h, nullptr);
+    CHECK(pool_alloc(&a, 5 * MiB) == hipSuccess && a == b);
+    CHECK(scratch_take(MiB, &h) == hipSuccess && h.p == p);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* name = argc > 1 ? argv[1] : "";
     if (!std::strcmp(name, "out_of_memory")) return out_of_memory();
+    if (!std::strcmp(name, "failed_wait")) return failed_wait();
     std::printf("no check of that name\n");
     return 2;
 }
