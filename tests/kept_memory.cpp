@@ -113,11 +113,51 @@ static int failed_wait()
     return 0;
 }
 
+// The idle memory stays within its bound, the blocks given back first go first,
+// and a block serves the next request of its size class.
+static int bound()
+{
+    void* p[40];
+    for (int i = 0; i < 40; ++i) CHECK(pool_alloc(&p[i], (60 + i % 3) * MiB) == hipSuccess);
+    std::set<void*> all(p, p + 40);
+    CHECK(all.size() == 40);
+    size_t held = g_used;
+    for (int i = 0; i < 40; ++i) {
+        const size_t before = kept(0)->pool.idle_bytes;
+        pool_free(p[i]);
+        CHECK(kept(0)->pool.idle_bytes <= kPoolBound);
+        if (before + pool_class(62 * MiB) <= kPoolBound) CHECK(g_used == held);   // nothing freed yet
+    }
+    size_t idle = 0;
+    for (auto& b : kept(0)->pool.idle) idle += b.first;
+    CHECK(idle == kept(0)->pool.idle_bytes && idle == g_used && kept(0)->pool.live.empty());
+    CHECK(idle + pool_class(62 * MiB) > kPoolBound);
+    CHECK(!g_held.count(p[0]) && g_held.count(p[39]));
+    const size_t n = kept(0)->pool.idle.size();
+    for (size_t i = 0; i < n; ++i) CHECK(kept(0)->pool.idle[i].second == p[40 - n + i]);
+    // the last block of the class is taken, another class is not
+    void* q = nullptr;
+    CHECK(pool_alloc(&q, 60 * MiB) == hipSuccess && q == p[39]);
+    pool_free(q);
+    CHECK(pool_alloc(&q, 33 * MiB) == hipSuccess && !all.count(q));
+    pool_free(q);
+    // larger than the bound: not kept
+    CHECK(pool_alloc(&q, kPoolBound + MiB) == hipSuccess);
+    pool_free(q);
+    CHECK(!g_held.count(q) && kept(0)->pool.idle_bytes <= kPoolBound);
+    // the classes: at least the request, at most an eighth more
+    for (size_t b = 1; b < 4 * MiB; b += 1 + b / 7) CHECK(pool_class(b) >= b && (b < 512 || pool_class(b) <= b + b / 8));
+    release_kept(*kept(0));
+    CHECK(g_used == 0 && kept(0)->pool.idle_bytes == 0);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* name = argc > 1 ? argv[1] : "";
     if (!std::strcmp(name, "out_of_memory")) return out_of_memory();
     if (!std::strcmp(name, "failed_wait")) return failed_wait();
+    if (!std::strcmp(name, "bound")) return bound();
     std::printf("no check of that name\n");
     return 2;
 }

@@ -20,7 +20,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["out_of_memory", "failed_wait"])
+@pytest.mark.parametrize("check", ["out_of_memory", "failed_wait", "bound"])
 def test_kept_memory(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
