@@ -573,3 +573,53 @@ def test_almost_a_lattice(dims):
     drop = np.all(ijk[:, :-1] == 0, 1)
     new = np.cumsum(~drop) - 1
     assert_same_mesh(x[~drop], new[cells[~drop[cells].any(1)]].astype(np.int32))
+
+
+def _is_lattice(x):
+    """Whether the steps back by more than half an axis' span stand, for every axis, at all
+    multiples of a number of points that divides the next slower axis' one."""
+    n, dim = x.shape
+    back = np.diff(x, axis=0) < -0.5 * (x.max(0) - x.min(0))
+    ends = sorted((np.flatnonzero(back[:, d]) + 1 for d in range(dim)), key=len)
+    period = n
+    for k, at in enumerate(ends):
+        if not np.array_equal(at, np.arange(period, n, period)):
+            return False
+        points = n // (len(ends[k + 1]) + 1) if k + 1 < dim else 1
+        if period % points or period // points < 2:
+            return False
+        period = points
+    return True
+
+
+@pytest.mark.parametrize("dims,order,drop", [
+    ((40, 30), "x", 1), ((40, 30), "y", 1), ((40, 30), "skip", 1), ((40, 30), "half", 1),
+    ((10, 7), "x", 7), ((10, 7), "x", 6), ((10, 7), "y", 5),        # 63, 64 and 65 points
+    ((11, 11, 11), "x", 1), ((11, 11, 11), "y", 1), ((11, 11, 11), "z", 1), ((5, 4, 4), "z", 15),
+])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_caller_order_axis_without_a_lattice(dims, order, drop, dtype):
+    """Every answer of the caller-order axis test on points that are no lattice (the
+    last ones and their cells left out): along each axis; two spacings a step or
+    half of them zero (no axis); below, at and above the sample's 64 points."""
+    if len(dims) == 2:
+        (nx, ny), (x, cells) = dims, meshes.jittered_tri_grid(*dims, seed=8, jitter=0.1)
+        i, j = (a.ravel() for a in np.meshgrid(np.arange(nx), np.arange(ny), indexing="xy"))
+        key = {"x": j * nx + i, "y": i * ny + j, "skip": j * nx + (i % 2) * nx * ny + i,
+               "half": (j // 2) * 2 * nx + 2 * i + j % 2}[order]
+    else:
+        x, cells, ijk = _lattice(dims, {"x": (2, 1, 0), "y": (0, 2, 1), "z": (0, 1, 2)}[order], 0.05)
+        key = np.arange(len(x))
+    rank = np.argsort(np.argsort(key, kind="stable"), kind="stable")
+    y = np.empty_like(x)
+    y[rank] = x
+    cells = rank[cells]
+    n = len(y) - drop
+    y, cells = y[:n].copy(), cells[(cells < n).all(1)].astype(np.int32)
+    assert not _is_lattice(y)
+    assert_same_mesh(y, cells, dtype)
+
+
+def test_the_lattice_check_sees_lattices():
+    for dims, order in (((40, 23), (0, 1)), ((9, 10, 11), (2, 0, 1))):
+        assert _is_lattice(_lattice(dims, order, 0.05)[0])
