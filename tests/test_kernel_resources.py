@@ -45,3 +45,17 @@ def test_no_scratch(asm):
 def test_no_packed_fp32(asm):
     for text in asm:
         assert not re.search(r"v_pk_(fma|mul|add)_f32", text)
+
+
+def test_no_scratch_in_any_kernel(asm):
+    """As test_no_scratch, for every kernel whatever its name, and no vector register spilled."""
+    names = []
+    for text in asm:
+        meta = text[text.index("amdhsa.kernels:"):]
+        for blk in re.split(r"\n  - (?=\.)", meta)[1:]:   # one kernel each
+            names.append(re.search(r"\n    \.name:\s+(\S+)", blk).group(1))
+            for what in ("private_segment_fixed_size", "vgpr_spill_count"):
+                n = int(re.search(r"\n    \.%s:\s+(\d+)" % what, blk).group(1))
+                assert n == 0, f"{names[-1]}: {what} {n}"
+    for kernel in ("ring_rows", "tile_record", "incidence_pass", "axis_slots", "normal_inverse", "scan_tiles"):
+        assert any(kernel in n for n in names), kernel
