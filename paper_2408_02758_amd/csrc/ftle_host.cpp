@@ -2363,7 +2363,7 @@ ftle_status ftle_batched(int n, const ftle_mesh_t* meshes, const void* const* fl
                                 call, tau, p->arg_storage.data(), p->args);
             hipKernelNodeParams kp{};
             kp.func = const_cast<void*>(batched_kernel_symbol(p->dim, p->f64, p->block, p->wide));
-    check_hip(allow_lds(kp.func, p->lds), "hipFuncSetAttribute");
+            check_hip(allow_lds(kp.func, p->lds), "hipFuncSetAttribute");
             kp.gridDim = dim3(p->grid);
             kp.blockDim = dim3(p->block);
             kp.sharedMemBytes = (unsigned)p->lds;
