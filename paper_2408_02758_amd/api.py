@@ -649,14 +649,15 @@ def forward_ell(coords: torch.Tensor, ell: torch.Tensor, flow: torch.Tensor, T: 
 
 
 def cached_memory_bytes() -> int:
-    """Device memory the mesh builds keep between calls (all devices)."""
+    """Device memory kept between calls and not in use by a mesh, in bytes (all devices): the builds'
+    scratch and, up to 1 GiB a device, the memory of destroyed meshes."""
     v = ctypes.c_int64(0)
     check(_lib.load().ftle_cached_memory_bytes(ctypes.byref(v)))
     return v.value
 
 
 def release_cached_memory() -> None:
-    """Free the device memory the mesh builds keep between calls."""
+    """Free the device memory kept between calls that no build is using (see cached_memory_bytes)."""
     check(_lib.load().ftle_release_cached_memory())
 
 

@@ -70,8 +70,9 @@ __device__ inline void flow_velocity(const FlowParams& pr, const double* p, doub
 //    to their own zero, 1/2 - |.|, and one sign for both products.  Odd
 //    polynomials keep a factor's relative exactness at its zero, so that a
 //    particle next to a wall leaves it as it should and one on a wall (y an
-//    integer, x = 0) has a normal velocity of exactly zero.  (Two sines of
-//    f + y and f - y would do, but their sum and difference cancel there.);
+//    integer, x = 0) has a normal velocity of exactly zero (two sines, of f + y
+//    and f - y, would do for all four, but their sum and difference cancel
+//    there: 4.09 ms where this takes 5.80, and 1e-16 absolute);
 //  - the ABC flow's six values come from three reductions to a quarter of a
 //    period, with the reduced argument's rounding carried along, so that its
 //    sines and cosines are as exact as the library's (rms error 2.8e-17);
@@ -81,10 +82,10 @@ __device__ inline void flow_velocity(const FlowParams& pr, const double* p, doub
 // most 0.6).  Against binary128 a double-gyre velocity's rms error is 4.8e-17
 // (5.5e-17 with the library's functions), 1.3e-16 of it next to a wall (1.6e-16);
 // an ABC velocity's 9.8e-17 (9.7e-17).
-// Vector instructions per step: double gyre 264 (library forms 435), ABC 505
-// (778), all issued back to back (4.2 cycles each).  1024 x 512 particles, 1500
-// double-gyre steps, float32: 5.61 ms (8.87); 81 x 67 x 59 particles, 500 ABC
-// steps, float64: 2.18 ms (3.54).
+// Vector instructions per step: double gyre 267 (library forms 435), ABC 506
+// (778), issued back to back.  1024 x 512 particles, 1500 double-gyre steps,
+// float32: 5.80 ms (8.86); 81 x 67 x 59 particles, 500 ABC steps, float64:
+// 2.17 ms (3.53).
 //
 // The bound is taken per block: over a whole path it grows with the square of
 // the duration and sent the double gyre to the library's forms from 7e4 time

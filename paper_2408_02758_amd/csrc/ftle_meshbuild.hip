@@ -1237,6 +1237,9 @@ hipError_t mb_tile_record(const int64_t* row_ptr, const int32_t* col, const uint
                           unsigned char* stage, hipStream_t s)
 {
     if (n_tiles == 0) return hipSuccess;
+    // The largest tile's words for every tile: a few long rows anywhere take
+    // workgroups from each CU (30 rows of 899 among 10^6 points: 0.09 -> 0.40 ms,
+    // the long rows' own work included, of a build of 12.1 ms).
     const size_t lds = 4 * (size_t)max_words;
     const hipError_t e = allow_lds(reinterpret_cast<const void*>(&tile_record), sizeof(TileScratch) + lds);
     if (e != hipSuccess) return e;
